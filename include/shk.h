@@ -464,6 +464,10 @@ int shk_profile_read_phases(double* ms, int n);
  *                           one): the lanes are split over workgroups and the
  *                           tail starts at the finest level where the coarser
  *                           levels of that many lanes fit
+ *   tail2d 0|32|64          2-D, one lane per tail workgroup: the tail whose cells
+ *                           sit in registers, from the finest level of at most
+ *                           that many cells a side (default 64; complex128 and
+ *                           chained legs 32); 0: the LDS tail
  *   mg_fuse 0|1             step fused with the finest restriction
  *   post_lt, down_lt, up_lt 2|4|8  lanes per thread (complex64, several lanes)
  *   lt64 0|2|4              lanes per thread on complex128

@@ -33,6 +33,7 @@ KINDS = {0: "2-D finite volume", 1: "3-D finite volume", 2: "CSR"}
 SPACE = {
     "tail_lds": [16384, 32768, 64512, 98304, 162816],
     "tail_lanes": [0, 1, 2, 4, 8],
+    "tail2d": [0, 32, 64],
     "mg_fuse": [0, 1],
     "post_lt": [0, 2, 4, 8],
     "down_lt": [2, 4, 8],
@@ -63,7 +64,7 @@ def knobs_for(key, n_lanes_real=None):
     mixed = prec == B.SHK_MIXED
     ks = ["cg_block", "graph", "asm_mfma"]
     if pc == B.SHK_PRECOND_MULTIGRID and kind in (0, 1):
-        ks += ["tail_lds"] + (["tail_lanes"] if lanes > 1 else [])
+        ks += ["tail_lds"] + (["tail_lanes"] if lanes > 1 else []) + (["tail2d"] if kind == 0 else [])
         if kind == 1:
             ks += ["tile3", "tile3_zb"] + (["tile3_lt"] if mixed else []) + (["tile3_post"] if lanes > 1 else [])
         if lanes == 1:

@@ -1412,6 +1412,408 @@ __global__ void __launch_bounds__(MG_TAIL_THREADS) k_mg_tail(MgTail a, c128 tau,
   for (int j = tid; j < n0; j += nth) xtop[gidx(j)] = sh[n0 + j];
 }
 
+// The coarse end of a 2-D V-cycle with one lane per workgroup, cells held in
+// registers.  What bounds it is the chain of phases (each a barrier and a round
+// of dependent LDS reads), so a phase here is as short as it can be: a thread
+// keeps its cell's right-hand side of every level in registers, the smoothed
+// value of a cell is formed once by its owner and published in LDS, and a phase
+// is one LDS write, one barrier, four LDS reads and the stencil.
+//
+// The base grid (the first level of at most 32 x 32 cells) is laid over the
+// 1024 threads in Morton order: thread t owns the cell whose interleaved
+// coordinate bits are t.  The four children of a coarse cell are then four
+// consecutive owners, and the cell itself is owned by the first of them, so
+// the cell of the j-th level above the base with Morton code m belongs to
+// thread m 4^j: restriction sums are cross-lane (a quad, then lanes 4 and 8
+// apart, then 16 and 32), and the parent's solution comes from a lane of the
+// same wave.  From the third level on at most 16 cells are left; wave 0 works
+// these alone, neighbours by cross-lane reads, without barriers.
+//
+// TOP4 (complex64): one more level of at most 64 x 64 cells on top, a 2 x 2
+// block of cells (one coarse cell's children) per thread.  The coefficients
+// come packed (k_mg_pack2): 8 values per cell of the base levels, the inverse
+// diagonal, the sum of all four faces, the mass and the four off-diagonal faces
+// (zero at the boundary), 7 per cell of the top level (its four faces, without
+// the sum), zeros outside the grid, in 16-byte chunks, chunk-major, so that
+// every load is coalesced; the base level's go to registers, the coarser
+// levels' to LDS.  Same per-cell expressions and children order as k_mg_down
+// and k_mg_up, with every multiply-add written out in the order in which the
+// compiler contracts them there (cmul_n, cmul_s, scale_add), so that a V-cycle
+// gives the same bits wherever its tail starts: a complex64 inner solve takes
+// another course for every bit that changes.
+//
+// Measured on MI355X: 32 x 32 complex64 cells and below 10.3 -> 5.7 us a launch
+// against k_mg_tail (512 x 512, one lane); complex128 7.2 us, where k_mg_tail took
+// 8.3 us from 16 x 16 on and two legs of 3.6 us above it; 64 x 64 complex64 9.1
+// us, for the 5.7 us and two legs of 4.5 us.  An idle launch takes 1.5 us.
+constexpr int T2_BASE = 32;                       // side of the base grid
+constexpr int T2_LV = 6;                          // base levels at most (32, 16, .., 1)
+constexpr int T2_SLOTS = 1024 + 256 + 64 + 16 + 4 + 1;
+constexpr int T2_TOPV = 28;                       // packed values per thread of the top level
+static_assert(T2_SLOTS * 8 * sizeof(double) <= MG_TAIL_LDS_MAX &&
+              (T2_SLOTS * 8 + 1024 * T2_TOPV) * sizeof(float) <= MG_TAIL_LDS_MAX, "the packed levels fit the tail's block");
+typedef float f4v __attribute__((ext_vector_type(4)));
+__host__ __device__ constexpr int t2_slots(int j) { return 1024 >> (2 * j); }
+__host__ __device__ constexpr int t2_slot0(int j) { return j == 0 ? 0 : t2_slot0(j - 1) + t2_slots(j - 1); }
+__host__ __device__ constexpr int t2_pitch(int j) { return (T2_BASE >> j) + 2; }   // one ring of zeros
+// LDS offset (elements) of the published values: base levels 0..2, then the top
+__host__ __device__ constexpr int t2_lds0(int j) { return j == 0 ? 0 : t2_lds0(j - 1) + t2_pitch(j - 1) * t2_pitch(j - 1); }
+constexpr int T2_EX = t2_lds0(3);                 // 16 exchange slots
+constexpr int T2_CF = T2_EX + 16;                 // coefficients of base levels 1..5, 4 elements a cell
+constexpr int T2_TOP0 = T2_CF + 4 * (T2_SLOTS - 1024);
+constexpr int T2_TOPP = 2 * T2_BASE + 2;
+__host__ __device__ constexpr int t2_lds_elems(bool top4) { return T2_TOP0 + (top4 ? T2_TOPP * T2_TOPP : 0); }
+
+// The even bits of a Morton code, packed.
+__host__ __device__ __forceinline__ int t2_even(int m) {
+  m &= 0x555;
+  m = (m | (m >> 1)) & 0x333;
+  m = (m | (m >> 2)) & 0x70f;
+  m = (m | (m >> 4)) & 0x3f;
+  return m;
+}
+
+template <typename R> struct T2Cell {
+  cx<R> d;      // inverse diagonal
+  R fsum, m;    // sum of the four faces, mass
+  R fo[4];      // off-diagonal faces
+};
+template <typename Op, typename R> struct T2Pack {
+  int J;                        // base levels
+  int tnx, tny;                 // top level (TOP4), or 0
+  Op top;
+  const cx<R>* tdinv;
+  int nx[T2_LV], ny[T2_LV];
+  Op op[T2_LV];
+  const cx<R>* dinv[T2_LV];
+};
+// One thread per packed cell, the base levels' first.
+template <typename Op, typename R>
+__global__ void __launch_bounds__(BS) k_mg_pack2(T2Pack<Op, R> p, R* __restrict__ dst) {
+  const int g = blockIdx.x * BS + threadIdx.x;
+  constexpr int E = 16 / (int)sizeof(R);   // values per chunk
+#pragma unroll
+  for (int j = 0; j < T2_LV; ++j) {
+    const int s = g - t2_slot0(j);
+    if (j >= p.J || s < 0 || s >= t2_slots(j)) continue;
+    const int x = t2_even(s), y = t2_even(s >> 1);
+    R v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (x < p.nx[j] && y < p.ny[j]) {
+      const int c = x + p.nx[j] * y;
+      int idx[4];
+      R fo[4], fsum;
+      p.op[j].template stencil_at<R>(x, y, 0, c, idx, fo, fsum);
+      const cx<R> d = p.dinv[j][c];
+      v[0] = d.re;
+      v[1] = d.im;
+      v[2] = fsum;
+      v[3] = (R)p.op[j].mass(c);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[4 + q] = fo[q];
+    }
+    R* out = dst + (size_t)t2_slot0(j) * 8;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) out[((q / E) * t2_slots(j) + s) * E + q % E] = v[q];
+  }
+  const int u = g - T2_SLOTS;
+  if (p.tnx == 0 || u < 0 || u >= 4096) return;
+  const int t = u >> 2, q = u & 3;
+  const int i = 2 * t2_even(t) + (q & 1), j = 2 * t2_even(t >> 1) + (q >> 1);
+  R v[7] = {0, 0, 0, 0, 0, 0, 0};
+  if (i < p.tnx && j < p.tny) {
+    const int c = i + p.tnx * j, fx = c + j;
+    const cx<R> d = p.tdinv[c];
+    v[0] = d.re;
+    v[1] = d.im;
+    v[2] = (R)p.top.tx[fx];
+    v[3] = (R)p.top.tx[fx + 1];
+    v[4] = (R)p.top.ty[c];
+    v[5] = (R)p.top.ty[c + p.tnx];
+    v[6] = (R)p.top.mass(c);
+  }
+  R* out = dst + (size_t)T2_SLOTS * 8;
+#pragma unroll
+  for (int e = 0; e < 7; ++e) {
+    const int w = 7 * q + e;
+    out[((w / E) * 1024 + t) * E + w % E] = v[e];
+  }
+}
+// Cell s of base level j; lv: the level's packed values (global memory or LDS).
+template <typename R> __device__ __forceinline__ T2Cell<R> t2_load(const R* lv, int j, int s) {
+  T2Cell<R> c;
+  if constexpr (sizeof(R) == 4) {
+    const f4v* p = reinterpret_cast<const f4v*>(lv);
+    const f4v a = p[s], b = p[t2_slots(j) + s];
+    c.d = cx<R>{a.x, a.y};
+    c.fsum = a.z;
+    c.m = a.w;
+    c.fo[0] = b.x; c.fo[1] = b.y; c.fo[2] = b.z; c.fo[3] = b.w;
+  } else {
+    const d2v* p = reinterpret_cast<const d2v*>(lv);
+    const int n = t2_slots(j);
+    const d2v a = p[s], b = p[n + s], e = p[2 * n + s], f = p[3 * n + s];
+    c.d = cx<R>{a.x, a.y};
+    c.fsum = b.x;
+    c.m = b.y;
+    c.fo[0] = e.x; c.fo[1] = e.y; c.fo[2] = f.x; c.fo[3] = f.y;
+  }
+  return c;
+}
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+// a b; imaginary part with a.re b.im fused (n), or a.im b.re (s)
+template <typename R> __device__ __forceinline__ cx<R> cmul_n(cx<R> a, cx<R> b) {
+  return cx<R>{fma_(a.re, b.re, -(a.im * b.im)), fma_(a.re, b.im, a.im * b.re)};
+}
+template <typename R> __device__ __forceinline__ cx<R> cmul_s(cx<R> a, cx<R> b) {
+  return cx<R>{fma_(a.re, b.re, -(a.im * b.im)), fma_(a.im, b.re, a.re * b.im)};
+}
+// s a + c
+template <typename R> __device__ __forceinline__ cx<R> scale_add(R s, cx<R> a, cx<R> c) {
+  return cx<R>{fma_(s, a.re, c.re), fma_(s, a.im, c.im)};
+}
+// A x from x at the cell and its neighbours; tn: which of the two products tr x
+template <typename R>
+__device__ __forceinline__ cx<R> t2_apply(const T2Cell<R>& c, cx<R> tr, bool tn, cx<R> xi, cx<R> xw, cx<R> xe,
+                                          cx<R> xs, cx<R> xn) {
+  const cx<R> tx{cmul_n(tr, xi).re, tn ? cmul_n(tr, xi).im : cmul_s(tr, xi).im};
+  cx<R> ax = scale_add(c.fsum, xi, c.m * tx);
+  ax = scale_add(-c.fo[0], xw, ax);
+  ax = scale_add(-c.fo[1], xe, ax);
+  ax = scale_add(-c.fo[2], xs, ax);
+  ax = scale_add(-c.fo[3], xn, ax);
+  return ax;
+}
+template <typename R> __device__ __forceinline__ cx<R> t2_xor_sum(cx<R> v, int m) {
+  v.re += __shfl_xor(v.re, m);
+  v.im += __shfl_xor(v.im, m);
+  v.re += __shfl_xor(v.re, 2 * m);
+  v.im += __shfl_xor(v.im, 2 * m);
+  return v;
+}
+template <typename R> __device__ __forceinline__ cx<R> t2_shfl(cx<R> v, int l) {
+  return cx<R>{__shfl(v.re, l), __shfl(v.im, l)};
+}
+template <typename R> __device__ __forceinline__ void t2_pin(cx<R>& v) { asm volatile("" : "+v"(v.re), "+v"(v.im)); }
+template <typename R> __device__ __forceinline__ void t2_pin(T2Cell<R>& c) {
+  asm volatile("" : "+v"(c.d.re), "+v"(c.d.im), "+v"(c.fsum), "+v"(c.m));
+  asm volatile("" : "+v"(c.fo[0]), "+v"(c.fo[1]), "+v"(c.fo[2]), "+v"(c.fo[3]));
+}
+
+// Workgroup g takes lane g of the 2^lSg that btop and xtop interleave.  nx, ny:
+// the level of btop, the top level (TOP4) or the base level; J base levels.
+// lanes_order: the top level rounds as k_mg_down_lanes and k_mg_up_lanes do,
+// else as k_mg_down and k_mg_up.
+template <typename R, bool TOP4>
+__global__ void __launch_bounds__(MG_TAIL_THREADS) k_mg_tail2d(int nx, int ny, int J, int lanes_order,
+                                                               c128 tau, double omega, int lSg,
+                                                               const R* __restrict__ pack,
+                                                               const cx<R>* __restrict__ btop,
+                                                               cx<R>* __restrict__ xtop,
+                                                               const CgScal* __restrict__ sc,
+                                                               const int* __restrict__ all_done) {
+  extern __shared__ __align__(16) char lds_raw[];
+  cx<R>* sh = reinterpret_cast<cx<R>*>(lds_raw);
+  constexpr int NT = TOP4 ? 4 : 1;
+  const int flag = *all_done;
+  const int stopped = lSg > 0 ? (int)sc[blockIdx.x].done : 0;
+  const int t = threadIdx.x, lane = t & (WAVE - 1);
+  const int X = t2_even(t), Y = t2_even(t >> 1);
+  const cx<R> tr = cvt<R>(tau);
+  const R om = (R)omega;
+  T2Cell<R> ct[NT];   // the top level's block (TOP4)
+  cx<R> bt[NT];
+  // the loads of the way down are issued together
+  if constexpr (TOP4) {
+    constexpr int E = 16 / (int)sizeof(R);
+    R v[T2_TOPV];
+    const R* tp = pack + (size_t)T2_SLOTS * 8;
+#pragma unroll
+    for (int g = 0; g < T2_TOPV / E; ++g) {
+      const f4v a = reinterpret_cast<const f4v*>(tp)[g * 1024 + t];
+      v[4 * g] = a.x; v[4 * g + 1] = a.y; v[4 * g + 2] = a.z; v[4 * g + 3] = a.w;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = 2 * X + (q & 1), j = 2 * Y + (q >> 1);
+      const R* c = v + 7 * q;
+      ct[q].d = cx<R>{c[0], c[1]};
+      ct[q].fsum = c[2] + c[3] + c[4] + c[5];
+      ct[q].fo[0] = i > 0 ? c[2] : (R)0;
+      ct[q].fo[1] = i < nx - 1 ? c[3] : (R)0;
+      ct[q].fo[2] = j > 0 ? c[4] : (R)0;
+      ct[q].fo[3] = j < ny - 1 ? c[5] : (R)0;
+      ct[q].m = c[6];
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < NT; ++q) {
+    const int i = TOP4 ? 2 * X + (q & 1) : X, j = TOP4 ? 2 * Y + (q >> 1) : Y;
+    const bool in = i < nx && j < ny;
+    const cx<R> v = btop[((long)(in ? i + nx * j : 0) << lSg) + blockIdx.x];
+    bt[q] = in ? v : cx<R>{0, 0};
+  }
+  T2Cell<R> cb0 = t2_load<R>(pack, 0, t);
+  {
+    // the coarser base levels' coefficients, to LDS as they are packed
+    constexpr int NCH = (T2_SLOTS - 1024) * 8 * (int)sizeof(R) / 16;
+    const d2v* src = reinterpret_cast<const d2v*>(pack + (size_t)1024 * 8);
+    d2v* dst = reinterpret_cast<d2v*>(sh + T2_CF);
+    d2v v0 = t < NCH ? src[t] : d2v{0, 0}, v1 = d2v{0, 0};
+    if (NCH > MG_TAIL_THREADS && t + MG_TAIL_THREADS < NCH) v1 = src[t + MG_TAIL_THREADS];
+    // zeros around the published values (each region's ring)
+    auto ring = [&](int base, int P, int e) {
+      const int s = e / (P - 1), o = e - s * (P - 1);
+      if (e >= 0 && e < 4 * (P - 1))
+        sh[base + (s == 0 ? o : s == 1 ? o * P + P - 1 : s == 2 ? P * P - 1 - o : (P - 1 - o) * P)] = cx<R>{0, 0};
+    };
+    ring(t2_lds0(0), t2_pitch(0), t);         // 132 cells
+    ring(t2_lds0(1), t2_pitch(1), t - 192);   // 68
+    ring(t2_lds0(2), t2_pitch(2), t - 320);   // 36
+    if constexpr (TOP4) ring(T2_TOP0, T2_TOPP, t - 384);   // 260
+#pragma unroll
+    for (int q = 0; q < NT; ++q) t2_pin(bt[q]);
+    t2_pin(cb0);
+    if (t < NCH) dst[t] = v0;
+    if (NCH > MG_TAIL_THREADS && t + MG_TAIL_THREADS < NCH) dst[t + MG_TAIL_THREADS] = v1;
+  }
+  if (flag || stopped) return;   // uniform: the whole workgroup leaves
+  __syncthreads();
+  const R* cl = reinterpret_cast<const R*>(sh + T2_CF);
+  auto lds_cell = [&](int j, int s) { return t2_load<R>(cl + (t2_slot0(j) - 1024) * 8, j, s); };
+  const int tp = T2_TOP0 + (2 * X + 1) + T2_TOPP * (2 * Y + 1);   // the block's first cell
+  // A v of the block from its own values and the published ring
+  // (o: the same with which the cell's own term is formed)
+  auto top_apply = [&](bool tn, const cx<R> (&o)[NT], const cx<R> (&v)[NT], cx<R> (&ax)[NT]) {
+    if constexpr (TOP4) {
+      const cx<R>* p = sh + tp;
+      ax[0] = t2_apply(ct[0], tr, tn, o[0], p[-1], v[1], p[-T2_TOPP], v[2]);
+      ax[1] = t2_apply(ct[1], tr, tn, o[1], v[0], p[2], p[1 - T2_TOPP], v[3]);
+      ax[2] = t2_apply(ct[2], tr, tn, o[2], p[T2_TOPP - 1], v[3], v[0], p[2 * T2_TOPP]);
+      ax[3] = t2_apply(ct[3], tr, tn, o[3], v[2], p[T2_TOPP + 2], v[1], p[2 * T2_TOPP + 1]);
+    }
+  };
+  auto top_publish = [&](const cx<R> (&v)[NT]) {
+    if constexpr (TOP4) {
+      sh[tp] = v[0];
+      sh[tp + 1] = v[1];
+      sh[tp + T2_TOPP] = v[2];
+      sh[tp + T2_TOPP + 1] = v[3];
+    }
+    __syncthreads();
+  };
+  cx<R> b[4], x{0, 0};   // right-hand sides of the base levels 0..3
+  if constexpr (TOP4) {
+    cx<R> x1[4], own[4], ax[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      x1[q] = om * cmul_s(ct[q].d, bt[q]);
+      own[q] = cx<R>{x1[q].re, lanes_order ? x1[q].im : om * cmul_n(ct[q].d, bt[q]).im};
+    }
+    top_publish(x1);
+    top_apply(true, own, x1, ax);
+    b[0] = ((bt[0] - ax[0]) + (bt[1] - ax[1])) + ((bt[2] - ax[2]) + (bt[3] - ax[3]));
+  } else {
+    b[0] = bt[0];
+  }
+  // base levels 0..2, down
+  auto slot = [&](int j) { return sh + t2_lds0(j) + ((X >> j) + 1) + t2_pitch(j) * ((Y >> j) + 1); };
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    if (j + 1 >= J) break;
+    const int P = t2_pitch(j);
+    const T2Cell<R> c = j == 0 ? cb0 : lds_cell(j, t >> (2 * j));
+    const bool owner = (t & ((1 << (2 * j)) - 1)) == 0;
+    cx<R>* p = slot(j);
+    if (owner) p[0] = om * cmul_s(c.d, b[j]);
+    __syncthreads();
+    cx<R> v = b[j] - t2_apply(c, tr, true, om * cmul_n(c.d, b[j]), p[-1], p[1], p[-P], p[P]);
+    if (j == 0) v = group_sum<4>(v);
+    else v = t2_xor_sum(v, 1 << (2 * j));
+    b[j + 1] = v;
+  }
+  // levels 3..5 (4 x 4 cells at most) on wave 0, Morton code in the lane's low
+  // four bits: one value from each wave, and one back
+  if (J > 3) {
+    cx<R>* ex = sh + T2_EX;
+    if (lane == 0) ex[t / WAVE] = b[3];
+    __syncthreads();
+    if (t < WAVE) {
+      const int l = t & 15;
+      cx<R> bw[3], xw[3];
+      T2Cell<R> cw[3];
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+        if (j + 3 < J) cw[j] = lds_cell(j + 3, l >> (2 * j));
+      bw[0] = ex[l];
+      // lane that owns cell (a, c) of level 3 + j, clamped to its 4 >> j square
+      auto own = [&](int j, int a, int c) {
+        const int W = (4 >> j) - 1;
+        a = a < 0 ? 0 : a > W ? W : a;
+        c = c < 0 ? 0 : c > W ? W : c;
+        return ((a & 1) | ((c & 1) << 1) | ((a & 2) << 1) | ((c & 2) << 2)) << (2 * j);
+      };
+      auto apply = [&](int j, bool tn, cx<R> o, cx<R> v) {
+        const int cx_ = t2_even(l) >> j, cy = t2_even(l >> 1) >> j;
+        return t2_apply(cw[j], tr, tn, o, t2_shfl(v, own(j, cx_ - 1, cy)), t2_shfl(v, own(j, cx_ + 1, cy)),
+                        t2_shfl(v, own(j, cx_, cy - 1)), t2_shfl(v, own(j, cx_, cy + 1)));
+      };
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        if (j + 4 >= J) break;
+        const cx<R> v = bw[j] - apply(j, true, om * cmul_n(cw[j].d, bw[j]), om * cmul_s(cw[j].d, bw[j]));
+        bw[j + 1] = j == 0 ? group_sum<4>(v) : t2_xor_sum(v, 4);
+      }
+#pragma unroll
+      for (int j = 2; j >= 0; --j) {
+        if (j + 3 >= J) continue;
+        if (j + 4 == J) {
+          xw[j] = cmul_s(cw[j].d, bw[j]);   // one cell
+        } else if (j < 2) {
+          const cx<R> xi = scale_add(om, cmul_s(cw[j].d, bw[j]), xw[j + 1]);
+          xw[j] = scale_add(om, cmul_s(cw[j].d, bw[j] - apply(j, false, xi, xi)), xi);
+        }
+      }
+      if (t < 16) ex[t] = xw[0];
+    }
+    __syncthreads();
+    x = ex[t / WAVE];
+  }
+  // base levels 2..0, up
+#pragma unroll
+  for (int j = 2; j >= 0; --j) {
+    if (j >= J) continue;
+    const T2Cell<R> c = j == 0 ? cb0 : lds_cell(j, t >> (2 * j));
+    if (j + 1 == J) {   // one cell
+      x = cmul_s(c.d, b[j]);
+      __syncthreads();  // the next finer level's published values have been read
+      continue;
+    }
+    const int P = t2_pitch(j);
+    const bool owner = (t & ((1 << (2 * j)) - 1)) == 0;
+    cx<R>* p = slot(j);
+    const cx<R> xi = scale_add(om, cmul_s(c.d, b[j]), x);
+    if (owner) p[0] = xi;
+    __syncthreads();
+    x = scale_add(om, cmul_s(c.d, b[j] - t2_apply(c, tr, false, xi, p[-1], p[1], p[-P], p[P])), xi);
+  }
+  if constexpr (TOP4) {
+    cx<R> x2[4], ax[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x2[q] = scale_add(om, cmul_s(ct[q].d, bt[q]), x);
+    top_publish(x2);
+    top_apply(lanes_order != 0, x2, x2, ax);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = 2 * X + (q & 1), j = 2 * Y + (q >> 1);
+      if (i < nx && j < ny) 
+        xtop[((long)(i + nx * j) << lSg) + blockIdx.x] = scale_add(om, cmul_s(ct[q].d, bt[q] - ax[q]), x2[q]);
+    }
+  } else {
+    if (X < nx && Y < ny) xtop[((long)(X + nx * Y) << lSg) + blockIdx.x] = x;
+  }
+}
+
 // The coarsest level solved on the grid (only when even its lanes exceed the
 // tail's LDS): x = D^-1 b.
 template <typename R>

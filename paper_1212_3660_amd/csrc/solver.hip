@@ -389,6 +389,8 @@ template <typename F, typename Fn> static int with_op(const shk_problem* p, Fn&&
 //  tail_lanes  lanes per workgroup of that tail (0: all; else the lanes are
 //              split over several workgroups, and the tail starts where the
 //              levels of that many lanes fit)
+//  tail2d      2-D, one lane per workgroup: the tail with its cells in registers,
+//              from the first level of at most tail2d x tail2d cells (0: none)
 //  mg_fuse     step fused with the finest restriction where it applies
 //  post_lt, down_lt, up_lt   lanes per thread of the product and grid legs
 //              (complex64, several lanes); lt64 the same on complex128
@@ -415,6 +417,7 @@ struct Tune {
   int stall_min = 150, stall_mult = 3;
   int tail_lds = MG_TAIL_LDS;
   int tail_lanes = 1;  // lanes per tail workgroup (0: all lanes in one)
+  int tail2d = 64;     // side of the finest level of the 2-D register tail (0: none)
   int mg_fuse = 1;
   int post_lt = 2;
   int down_lt = 4, up_lt = 4;
@@ -447,6 +450,7 @@ struct Tune {
     else if (k == "stall_mult") { if (iv < 0) return false; stall_mult = iv; }
     else if (k == "tail_lds") { if (iv < 0 || iv > MG_TAIL_LDS_MAX) return false; tail_lds = iv; }
     else if (k == "tail_lanes") { if (iv < 0 || iv > 64 || (iv & (iv - 1))) return false; tail_lanes = iv; }
+    else if (k == "tail2d") { if (iv != 0 && iv != 32 && iv != 64) return false; tail2d = iv; }
     else if (k == "mg_fuse") { mg_fuse = iv != 0; }
     else if (k == "post_lt") { post_lt = iv >= 8 ? 8 : iv >= 4 ? 4 : iv >= 2 ? 2 : 0; }
     else if (k == "down_lt") { down_lt = chunk(iv); }
@@ -478,6 +482,7 @@ struct Tune {
     else if (k == "stall_mult") *v = stall_mult;
     else if (k == "tail_lds") *v = tail_lds;
     else if (k == "tail_lanes") *v = tail_lanes;
+    else if (k == "tail2d") *v = tail2d;
     else if (k == "mg_fuse") *v = mg_fuse;
     else if (k == "post_lt") *v = post_lt;
     else if (k == "down_lt") *v = down_lt;
@@ -1174,7 +1179,28 @@ template <typename R, typename Op, typename OpD> struct Group {
         k_mg_dinv_levels<OpD, R><<<grid_items(tot, 2048), BS, 0, st>>>(tab, tau);
       }
       const int t = mg_tail_level(ilog2(S));
-      if (t < mg_levels()) {
+      if (tail2d_level(ilog2(S)) == t) {
+        if constexpr (Op::NB == 4) {
+          T2Pack<Op, R> pk{};
+          const int t0 = t + (tail2d_top4(t) ? 1 : 0);
+          pk.J = mg_levels() - t0;
+          for (int j = 0; j < pk.J; ++j) {
+            const LevelDims d = mg_dims(t0 + j);
+            pk.nx[j] = d.nx;
+            pk.ny[j] = d.ny;
+            pk.op[j] = mg_op<Op, R>(op, t0 + j);
+            pk.dinv[j] = lvl_dinv(t0 + j);
+          }
+          if (t0 > t) {
+            const LevelDims d = mg_dims(t);
+            pk.tnx = d.nx;
+            pk.tny = d.ny;
+            pk.top = mg_op<Op, R>(op, t);
+            pk.tdinv = lvl_dinv(t);
+          }
+          k_mg_pack2<Op, R><<<(T2_SLOTS + (t0 > t ? 4096 : 0) + BS - 1) / BS, BS, 0, st>>>(pk, (R*)B.mpack);
+        }
+      } else if (t < mg_levels()) {
         MgPack pk;
         mg_tail_layout(t, tail_lg(ilog2(S)), mg_ta, pk, mg_lds);
         k_mg_pack<<<pk.nseg, BS, 0, st>>>(pk, B.mpack);
@@ -1208,9 +1234,32 @@ template <typename R, typename Op, typename OpD> struct Group {
     const int tl = tn().tail_lanes;
     return tl > 0 ? std::min(lS, ilog2(tl)) : lS;
   }
-  // First level of the tail: the finest level from which all coarser levels
-  // of one tail workgroup's lanes fit in its LDS.
+  // First level of the register tail (2-D, one lane per workgroup): the finest
+  // level of at most tail2d x tail2d cells; at most 32 x 32 for complex128 (a
+  // block of four such cells does not fit a thread's 128 registers), where the
+  // legs above are chained (one leg more in a chain costs 0.5 us, the 64 x 64
+  // level here 3.4 us; a leg of its own 4.5 us) and for one lane's finest
+  // level, which the fused step restricts; -1 where that tail does not apply.
+  int tail2d_level(int lS) const {
+    if (Op::NB != 4 || tn().tail2d <= 0 || tail_lg(lS) != 0) return -1;
+    for (int l = 0; l < mg_levels(); ++l) {
+      const LevelDims d = mg_dims(l);
+      const bool four = c64 && !chain_ok(lS) && (lS > 0 || l > 0);
+      const int side = four ? tn().tail2d : std::min(tn().tail2d, T2_BASE);
+      if (d.nx <= side && d.ny <= side) return l <= lds_tail_level(lS) ? l : -1;
+    }
+    return -1;
+  }
+  bool tail2d_top4(int t) const { return mg_dims(t).nx > T2_BASE || mg_dims(t).ny > T2_BASE; }
+  // First level of the tail: the register tail's where it starts no later
+  // (each level more is two launches less), else the LDS tail's.
   int mg_tail_level(int lS) const {
+    const int t2 = tail2d_level(lS);
+    return t2 >= 0 ? t2 : lds_tail_level(lS);
+  }
+  // The finest level from which all coarser levels of one tail workgroup's
+  // lanes fit in its LDS.
+  int lds_tail_level(int lS) const {
     const int Lv = mg_levels(), lg = tail_lg(lS);
     int t = Lv;
     for (int l = Lv - 1; l >= 0; --l) {
@@ -1386,6 +1435,25 @@ template <typename R, typename Op, typename OpD> struct Group {
       k_mg_up_chain2d<Op, R, 16><<<g, BS, 0, st>>>(c, tau, mg_omega, B.all_done);
     }
   }
+  void tail2d(int t, unsigned gt, c128 tau, int lS, const cx<R>* bl, cx<R>* xt) {
+    if constexpr (Op::NB == 4) {
+      const LevelDims d = mg_dims(t);
+      const bool top4 = tail2d_top4(t);
+      const int J = mg_levels() - t - (top4 ? 1 : 0);
+      const size_t lds = (size_t)t2_lds_elems(top4) * sizeof(cx<R>);
+      auto go = [&](auto kern) {
+        kern<<<gt, MG_TAIL_THREADS, lds, st>>>(d.nx, d.ny, J, lS > 0 && t < lds_tail_level(lS) ? 1 : 0, tau, mg_omega,
+                                               lS, (const R*)B.mpack, bl, xt, vsc, B.all_done);
+      };
+      if constexpr (c64) {
+        if (top4) {
+          go(k_mg_tail2d<R, true>);
+          return;
+        }
+      }
+      go(k_mg_tail2d<R, false>);
+    }
+  }
   void mg_vcycle(const cx<R>* b0, c128 tau, int lS, cx<R>* uout, int from = 0) {
     if constexpr (Op::NB > 0) {
       const int Lv = mg_levels();
@@ -1417,7 +1485,8 @@ template <typename R, typename Op, typename OpD> struct Group {
         cx<R>* xt = t == 0 ? uout : B.mx[t - 1];   // mg_ta, mg_lds: laid out by mg_prepare
         const int lg = tail_lg(lS);
         const unsigned gt = 1u << (lS - lg);
-        if (mg_lds > MG_TAIL_LDS)
+        if (tail2d_level(lS) == t) tail2d(t, gt, tau, lS, bl, xt);
+        else if (mg_lds > MG_TAIL_LDS)
           k_mg_tail<Op, R, MG_TAIL_LDS_MAX><<<gt, MG_TAIL_THREADS, (size_t)mg_lds, st>>>(
               mg_ta, tau, mg_omega, lg, lS, B.mpack, bl, xt, vsc, B.all_done);
         else
@@ -1794,7 +1863,10 @@ template <typename R, typename Op, typename OpD> struct Group {
       bytes += nl * (S * w + w + fpc + mass) + nc * S * w;              // down
       bytes += nl * (S * w + w + fpc + mass + S * w) + nc * S * w;      // up
     }
-    if (t < Lv) bytes += 2.0 * mg_dims(t).n() * S * w + 4.0 * mg_ta.pack_words;   // tail in/out, coefficients
+    if (t < Lv)   // tail in/out, coefficients
+      bytes += 2.0 * mg_dims(t).n() * S * w +
+               (tail2d_level(lS) == t ? (T2_SLOTS * 8.0 + (tail2d_top4(t) ? 1024.0 * T2_TOPV : 0.0)) * sizeof(R)
+                                      : 4.0 * mg_ta.pack_words);
     bytes += (double)N * 3.0 * w + (double)n * fpc;                     // product
     return bytes;
   }
