@@ -88,15 +88,15 @@ __device__ __forceinline__ void lds_sync() {
 }
 
 // Block partial per lane: wave tree over lanes of equal r, then the waves in
-// order.  Writes out[q*S + r] for r < S.
-template <int NV, int BSZ = BS>
+// order, of the block's first USE threads.  Writes out[q*S + r] for r < S.
+template <int NV, int BSZ = BS, int USE = BSZ>
 __device__ __forceinline__ void block_partials(c128 (&v)[NV], int S, c128* __restrict__ out) {
-  constexpr int NW = BSZ / WAVE;
+  constexpr int NW = USE / WAVE;
   __shared__ c128 sh[NW][NV][WAVE];
   const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
 #pragma unroll
   for (int q = 0; q < NV; ++q) v[q] = wave_sum_strided(v[q], S);
-  if (lane < S) {
+  if (lane < S && wv < NW) {
 #pragma unroll
     for (int q = 0; q < NV; ++q) sh[wv][q][lane] = v[q];
   }
@@ -802,8 +802,10 @@ __global__ void __launch_bounds__(BS) k_diag(OpD opd, long n, double* __restrict
 
 // -------------------------------------------------- Gram-Schmidt (CGS2) ----
 // Partial products v_i^H w over a block of items for columns i < kc.  Wave w
-// of the block handles columns w, w+NWAVE, ...; each lane runs over the items
-// at stride 64 (its rhs lane stays fixed), then a wave tree per lane group.
+// of block (x, y) of a grid (G, Y) handles columns w + 4 y, stepping 4 Y; each
+// lane runs over the items at stride 64 (its rhs lane stays fixed), then a wave
+// tree per lane group.  Y > 1 (dot_cols) where G blocks alone leave the chip
+// short of waves; it changes no sum.
 template <typename R>
 __global__ void __launch_bounds__(BS) k_gs_dot(long N, int S, int kc, const cx<R>* __restrict__ V,
                                                size_t cstride, const cx<R>* __restrict__ w,
@@ -811,7 +813,7 @@ __global__ void __launch_bounds__(BS) k_gs_dot(long N, int S, int kc, const cx<R
   const long start = blockIdx.x * ipb;
   const long end = start + ipb < N ? start + ipb : N;
   const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
-  for (int i = wv; i < kc; i += NWAVE) {
+  for (int i = wv + NWAVE * (int)blockIdx.y; i < kc; i += NWAVE * (int)gridDim.y) {
     const cx<R>* Vi = V + (size_t)i * cstride;
     // exact products of the stored values, FP64 sums (the projections in the
     // second pass are small differences of large terms)
@@ -823,60 +825,93 @@ __global__ void __launch_bounds__(BS) k_gs_dot(long N, int S, int kc, const cx<R
   }
 }
 
-// One block per (column i, lane r): sum the partials over G blocks.
+// One block per (column i, lane r), entry e = i S + r: sum the partials over G
+// blocks.  The entries of a 128-byte line of the partials go to blocks of one
+// XCD (as in k_lane_totals): with 64 lanes and 21 columns 57 -> 14 us.
 __global__ void __launch_bounds__(BS) k_gs_reduce(const c128* __restrict__ part, int G, int kc, int S,
                                                   c128* __restrict__ main_out, c128* __restrict__ aux_out,
                                                   int accumulate) {
-  const int i = blockIdx.x / S, r = blockIdx.x % S;
+  const int q = (int)blockIdx.x;
+  const int e = (((q >> 6) * 8 + (q & 7)) * 8) + ((q >> 3) & 7);
+  const int E = kc * S;
+  if (e >= E) return;
   c128 a{0.0, 0.0};
-  for (int b = threadIdx.x; b < G; b += BS) a = a + part[((size_t)b * kc + i) * S + r];
+#pragma unroll 4
+  for (int b = threadIdx.x; b < G; b += BS) a = a + part[(size_t)b * E + e];
   a = block_sum_all(a);
   if (threadIdx.x == 0) {
-    aux_out[i * S + r] = a;
-    main_out[i * S + r] = accumulate ? main_out[i * S + r] + a : a;
+    aux_out[e] = a;
+    main_out[e] = accumulate ? main_out[e] + a : a;
   }
 }
 
 // w -= sum_i h_i v_i for each item; optionally partials of the FP64 norm
-// ||w||^2 per lane (k_final_sqrt turns them into h_{k+1,k}).
-constexpr int GSQ = 4;
-template <typename R>
-__global__ void __launch_bounds__(BS) k_gs_update(long N, int S, int kc, const cx<R>* __restrict__ V,
-                                                  size_t cstride, const c128* __restrict__ h,
-                                                  cx<R>* __restrict__ w, int with_norm,
-                                                  c128* __restrict__ part) {
+// ||w||^2 per lane (k_final_sqrt turns them into h_{k+1,k}).  A block takes GSQ
+// BS items, a thread Q of them (tid, tid + GSQ BS / Q, ..).  Q = 1 while the
+// basis is in cache, where the kernel is bound by the latency of its column loop:
+// a thread per item and the loads of GSU columns in flight (512 x 512, complex64,
+// 24 columns: 31 -> 13.5 us); Q = GSQ from 1 Mi items up, where it streams and a
+// coefficient load should serve several items (256 x 256 x 64 lanes: 65 us, 74 with
+// Q = 1).  The block's norm sums the items tid, tid + BS, .. of tid < BS first,
+// whatever Q.
+constexpr int GSQ = 4, GSU = 8;
+template <typename R, int Q>
+__global__ void __launch_bounds__(BS * GSQ / Q) k_gs_update(long N, int S, int kc, const cx<R>* __restrict__ V,
+                                                            size_t cstride, const c128* __restrict__ h,
+                                                            cx<R>* __restrict__ w, int with_norm,
+                                                            c128* __restrict__ part) {
+  static_assert(Q == 1 || Q == GSQ, "items per thread");
+  constexpr int BT = BS * GSQ / Q;
   const int r = threadIdx.x & (S - 1);
-  const long base = (long)blockIdx.x * BS * GSQ + threadIdx.x;
+  const long base = (long)blockIdx.x * (BS * GSQ) + threadIdx.x;
   // the update runs in FP64 and w is rounded to its storage precision once:
   // after the projection w is a small difference of large terms
-  c128 wq[GSQ];
+  c128 a[Q];
 #pragma unroll
-  for (int qq = 0; qq < GSQ; ++qq) {
-    const long t = base + (long)qq * BS;
-    wq[qq] = t < N ? cvt<double>(w[t]) : c128{0, 0};
-  }
-  for (int i = 0; i < kc; ++i) {
-    const c128 hi = h[i * S + r];
-    const cx<R>* Vi = V + (size_t)i * cstride;
+  for (int q = 0; q < Q; ++q) a[q] = base + q * BT < N ? cvt<double>(w[base + q * BT]) : c128{0, 0};
+  if constexpr (Q == 1) {
+    const cx<R>* Vt = V + (base < N ? base : 0);
+    for (int i = 0; i < kc; i += GSU) {
+      cx<R> v[GSU];
 #pragma unroll
-    for (int qq = 0; qq < GSQ; ++qq) {
-      const long t = base + (long)qq * BS;
-      if (t < N) wq[qq] = wq[qq] - hi * cvt<double>(Vi[t]);
+      for (int u = 0; u < GSU; ++u) v[u] = i + u < kc ? Vt[(size_t)(i + u) * cstride] : cx<R>{0, 0};
+#pragma unroll
+      for (int u = 0; u < GSU; ++u)
+        if (i + u < kc) a[0] = a[0] - h[(i + u) * S + r] * cvt<double>(v[u]);
+    }
+  } else {
+    for (int i = 0; i < kc; ++i) {
+      const c128 hi = h[i * S + r];
+      const cx<R>* Vi = V + (size_t)i * cstride;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const long t = base + q * BT;
+        if (t < N) a[q] = a[q] - hi * cvt<double>(Vi[t]);
+      }
     }
   }
-  double a = 0.0;
+  double n2[Q], s = 0.0;
 #pragma unroll
-  for (int qq = 0; qq < GSQ; ++qq) {
-    const long t = base + (long)qq * BS;
-    if (t < N) {
-      const cx<R> ws = cvt<R>(wq[qq]);
-      w[t] = ws;
-      a += abs2(cvt<double>(ws));
-    }
+  for (int q = 0; q < Q; ++q) {
+    const long t = base + q * BT;
+    const cx<R> ws = cvt<R>(a[q]);
+    if (t < N) w[t] = ws;
+    n2[q] = t < N ? abs2(cvt<double>(ws)) : 0.0;
+    s += n2[q];
   }
+  if constexpr (Q == 1) {
   if (!with_norm) return;
-  c128 acc[1] = {{a, 0.0}};
-  block_partials<1>(acc, S, part + (size_t)blockIdx.x * S);
+    __shared__ double sh[BT];
+    sh[threadIdx.x] = s;
+    __syncthreads();
+    s = 0.0;
+    if (threadIdx.x < BS) {
+#pragma unroll
+      for (int q = 0; q < GSQ; ++q) s += sh[threadIdx.x + q * BS];
+    }
+  }
+  c128 acc[1] = {{s, 0.0}};
+  block_partials<1, BT, BS>(acc, S, part + (size_t)blockIdx.x * S);
 }
 
 // v_{k+1} = w / h_{k+1,k}; lanes that broke down (h <= 1e-14 ||M z||, section

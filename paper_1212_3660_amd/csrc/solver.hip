@@ -780,6 +780,20 @@ static long dot_ipb(long N) {
   return ipb;
 }
 
+// Column groups of its grid: below 4 Mi items its blocks are 8 waves per CU or
+// fewer, each with a column's loads in flight, and the four waves of a block
+// take a column each (512 x 512, complex64, 24 columns: 21 -> 12 us).  Larger
+// ones stream, and w is read once for all columns.
+static int dot_cols(long N, int kc) { return N >= (4L << 20) ? 1 : (kc + NWAVE - 1) / NWAVE; }
+static int gs_entries_grid(int entries) { return 64 * (((entries + 7) / 8 + 7) / 8); }
+
+template <typename R>
+static void gs_update(int Gu, long N, int S, int kc, const cx<R>* V, const c128* h, cx<R>* w, int with_norm,
+                      c128* part, hipStream_t st) {
+  if (N < (1L << 20)) k_gs_update<R, 1><<<Gu, BS * GSQ, 0, st>>>(N, S, kc, V, (size_t)N, h, w, with_norm, part);
+  else k_gs_update<R, GSQ><<<Gu, BS, 0, st>>>(N, S, kc, V, (size_t)N, h, w, with_norm, part);
+}
+
 // Gram-Schmidt of w against kc columns of V (Algorithm 3): CGS2, two block
 // passes (dot products of every column, then one update), or the paper's MGS,
 // one column at a time (its dot product, then its update).  H receives the kc
@@ -793,17 +807,17 @@ static void gram_schmidt(long N, int S, int kc, cx<R>* V, cx<R>* w, c128* H, c12
   const int Gu = (int)((N + (long)BS * GSQ - 1) / ((long)BS * GSQ));
   if (!mgs) {
     for (int pass = 0; pass < 2; ++pass) {
-      k_gs_dot<R><<<Gd, BS, 0, st>>>(N, S, kc, V, (size_t)N, w, part, ipb);
-      k_gs_reduce<<<kc * S, BS, 0, st>>>(part, Gd, kc, S, H, h2, pass);
-      k_gs_update<R><<<Gu, BS, 0, st>>>(N, S, kc, V, (size_t)N, h2, w, pass, part);
+      k_gs_dot<R><<<dim3(Gd, dot_cols(N, kc)), BS, 0, st>>>(N, S, kc, V, (size_t)N, w, part, ipb);
+      k_gs_reduce<<<gs_entries_grid(kc * S), BS, 0, st>>>(part, Gd, kc, S, H, h2, pass);
+      gs_update<R>(Gu, N, S, kc, V, h2, w, pass, part, st);
     }
     return;
   }
   for (int i = 0; i < kc; ++i) {
     cx<R>* Vi = V + (size_t)i * N;
     k_gs_dot<R><<<Gd, BS, 0, st>>>(N, S, 1, Vi, (size_t)N, w, part, ipb);
-    k_gs_reduce<<<S, BS, 0, st>>>(part, Gd, 1, S, H + (size_t)i * S, h2, 0);
-    k_gs_update<R><<<Gu, BS, 0, st>>>(N, S, 1, Vi, (size_t)N, h2, w, i == kc - 1 ? 1 : 0, part);
+    k_gs_reduce<<<gs_entries_grid(S), BS, 0, st>>>(part, Gd, 1, S, H + (size_t)i * S, h2, 0);
+    gs_update<R>(Gu, N, S, 1, Vi, h2, w, i == kc - 1 ? 1 : 0, part, st);
   }
 }
 
