@@ -12,6 +12,7 @@
 // order, redundantly in every block that needs them.  Repeated runs give
 // bitwise identical results.
 #pragma once
+#include <algorithm>
 #include "common.hpp"
 #include "ops.hpp"
 #include "../../include/shk.h"
@@ -1618,8 +1619,7 @@ __global__ void __launch_bounds__(BS) k_assemble_lds(long n, int S, int s_real, 
 // ------------------------------------------------------ true residuals -----
 // Partial ||b_r - (K + sigma_j M) x_{j,r}||^2 (mode 0) or conj(rs_r)^T
 // (b_r - (K + sigma_j M) x_{j,r}) (mode 1) per block; blockIdx.y = shift,
-// blockIdx.z = rhs; cells over blockIdx.x in y-slabs per XCD (SlabWalk), so
-// the neighbours' x comes from the XCD's own L2.
+// blockIdx.z = rhs; cells over blockIdx.x.  CSR problems; grids use k_resid_fv.
 template <typename Op>
 __global__ void __launch_bounds__(BS) k_resid(Op op, long n, int S, int nf, const c128* __restrict__ sigma,
                                               const c128* __restrict__ bint, const c128* __restrict__ X,
@@ -1642,7 +1642,7 @@ __global__ void __launch_bounds__(BS) k_resid(Op op, long n, int S, int nf, cons
 
 // The same for JR shifts per block (blockIdx.y = block of JR shifts): with
 // several lanes b and rs are strided by S (one cache line per lane and cell),
-// so each cell's b, rs, faces and mass are loaded once for JR shifts.
+// so each cell's b, rs and mass are loaded once for JR shifts.
 template <typename Op, int JR>
 __global__ void __launch_bounds__(BS) k_resid_jr(Op op, long n, int S, int nf, const c128* __restrict__ sigma,
                                                  const c128* __restrict__ bint, const c128* __restrict__ X,
@@ -1672,6 +1672,134 @@ __global__ void __launch_bounds__(BS) k_resid_jr(Op op, long n, int S, int nf, c
   for (int q = 0; q < JR; ++q) {
     const c128 t = block_sum_all(a[q]);
     if (q < nj && threadIdx.x == 0) part[((size_t)r * nf + j0 + q) * gridDim.x + blockIdx.x] = t;
+  }
+}
+
+// The same on a grid operator, JR shifts per block.  The launch reads X once and
+// is bound by that read, so a wave marches RESID_YB rows of 64 cells with the
+// row's x and the rows before and after it in registers for every shift: one
+// load of X per cell and shift, the x neighbours from the lanes beside (the
+// wave's two end lanes load theirs), faces and b once for JR shifts.  In 3-D the
+// four waves of a block march the same rows of four adjacent planes and load the
+// planes before and after, mostly from the CU's L1; in 2-D they take four
+// adjacent row segments.  Tiles (planes, rows, segments, the last fastest) go
+// over the grid in XCD bands.  512 x 512 x 200 shifts: 397 us with a cell's five
+// values loaded at every cell and indices divided, now 190 us.
+constexpr int RESID_YB = 16;
+template <typename Op> struct ResidTiles {   // tiles along x, y and z
+  int x, y, z;
+  __host__ __device__ explicit ResidTiles(const Op& op) {
+    const int segs = (op.nx + WAVE - 1) / WAVE;
+    x = segs;
+    z = 1;
+    if constexpr (Op::NB == 6) z = (op.nz + NWAVE - 1) / NWAVE;
+    else x = (segs + NWAVE - 1) / NWAVE;
+    y = (op.ny + RESID_YB - 1) / RESID_YB;
+  }
+};
+template <typename Op> static int resid_fv_tiles(const Op& op) {
+  const ResidTiles<Op> t(op);
+  return (int)std::min<long>((long)t.x * t.y * t.z, 1L << 30);
+}
+template <typename Op, int JR, int MODE>
+__global__ void __launch_bounds__(BS) k_resid_fv(Op op, int S, int nf, const c128* __restrict__ sigma,
+                                                 const c128* __restrict__ bint, const c128* __restrict__ X,
+                                                 const c128* __restrict__ rs, c128* __restrict__ part) {
+  constexpr bool D3 = Op::NB == 6;
+  const int nx = op.nx, ny = op.ny;
+  int nz = 1;
+  if constexpr (D3) nz = op.nz;
+  const long n = (long)nx * ny * nz;
+  const int pl = nx * ny;
+  const int j0 = blockIdx.y * JR, r = blockIdx.z;
+  const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+  const ResidTiles<Op> tl(op);
+  const int tx_ = tl.x, ty_ = tl.y, tiles = tl.x * tl.y * tl.z;
+  const c128* xj[JR];
+  c128 sg[JR], acc[JR];
+#pragma unroll
+  for (int q = 0; q < JR; ++q) {
+    const int j = j0 + q < nf ? j0 + q : nf - 1;
+    xj[q] = X + n * ((long)j + (long)nf * r);
+    sg[q] = sigma[j];
+    acc[q] = c128{0.0, 0.0};
+  }
+  for (int b = xcd_tile(blockIdx.x, gridDim.x); b < tiles; b += gridDim.x) {
+    const int bx = b % tx_, by = (b / tx_) % ty_, bz = b / (tx_ * ty_);
+    const int i = (D3 ? bx : bx * NWAVE + wv) * WAVE + lane, k = D3 ? bz * NWAVE + wv : 0;
+    const int y0 = by * RESID_YB, y1 = min(y0 + RESID_YB, ny);
+    const bool own = i < nx && k < nz;
+    if ((D3 ? bx : bx * NWAVE + wv) * WAVE >= nx || k >= nz) continue;   // whole waves
+    const int ic = own ? i : nx - 1;
+    const int c0 = ic + pl * k;
+    // the end lanes' outer neighbours (lane 0: i - 1, the last lane: i + 1)
+    const bool endl = lane == 0 ? i > 0 : lane == WAVE - 1 ? i < nx - 1 : false;
+    const int de = lane == 0 ? -1 : 1;
+    c128 xp[JR], xc[JR];
+#pragma unroll
+    for (int q = 0; q < JR; ++q) {
+      xp[q] = y0 > 0 ? xj[q][c0 + nx * (y0 - 1)] : c128{0.0, 0.0};
+      xc[q] = xj[q][c0 + nx * y0];
+    }
+    const int fy0 = ic + nx * (ny + 1) * k;   // ty of row 0
+    double fs = op.ty[fy0 + nx * y0];
+    for (int y = y0; y < y1; ++y) {
+      const int c = c0 + nx * y;
+      const bool up = y + 1 < ny;
+      c128 xn[JR], xe[JR], xd[D3 ? JR : 1], xu[D3 ? JR : 1];
+#pragma unroll
+      for (int q = 0; q < JR; ++q) {
+        xn[q] = up ? xj[q][c + nx] : c128{0.0, 0.0};
+        xe[q] = endl ? xj[q][c + de] : c128{0.0, 0.0};
+        if constexpr (D3) {
+          xd[q] = k > 0 ? xj[q][c - pl] : c128{0.0, 0.0};
+          xu[q] = k < nz - 1 ? xj[q][c + pl] : c128{0.0, 0.0};
+        }
+      }
+      const int fx = ic + (nx + 1) * (y + ny * k);
+      const double fw = op.tx[fx], fe = op.tx[fx + 1], fn = op.ty[fy0 + nx * (y + 1)];
+      double fd = 0.0, fu = 0.0;
+      if constexpr (D3) {
+        fd = op.tz[c];
+        fu = op.tz[c + pl];
+      }
+      const double m = op.mass(c);
+      const c128 bc = bint[(long)c * S + r];
+      c128 rc{0.0, 0.0};
+      if constexpr (MODE == 1) rc = rs[(long)c * S + r];
+      const double fsum = D3 ? fw + fe + fs + fn + fd + fu : fw + fe + fs + fn;
+      // a neighbour outside the grid counts zero
+      const double ow = i > 0 ? fw : 0.0, oe = i < nx - 1 ? fe : 0.0;
+#pragma unroll
+      for (int q = 0; q < JR; ++q) {
+        c128 lo{__shfl_up(xc[q].re, 1), __shfl_up(xc[q].im, 1)};
+        c128 hi{__shfl_down(xc[q].re, 1), __shfl_down(xc[q].im, 1)};
+        if (lane == 0) lo = xe[q];
+        if (lane == WAVE - 1) hi = xe[q];
+        c128 ax = fsum * xc[q] + m * (sg[q] * xc[q]);
+        ax = ax - ow * lo;
+        ax = ax - oe * hi;
+        ax = ax - fs * xp[q];
+        ax = ax - fn * xn[q];
+        if constexpr (D3) {
+          ax = ax - fd * xd[q];
+          ax = ax - fu * xu[q];
+        }
+        const c128 res = bc - ax;
+        if (own) {
+          if constexpr (MODE == 0) acc[q].re += abs2(res);
+          else acc[q] = acc[q] + cdot(rc, res);
+        }
+        xp[q] = xc[q];
+        xc[q] = xn[q];
+      }
+      fs = fn;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < JR; ++q) {
+    const c128 t = block_sum_all(acc[q]);
+    if (j0 + q < nf && threadIdx.x == 0) part[((size_t)r * nf + j0 + q) * gridDim.x + blockIdx.x] = t;
   }
 }
 

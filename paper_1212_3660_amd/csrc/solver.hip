@@ -2125,8 +2125,14 @@ template <typename R, typename Op, typename OpD> struct Group {
 template <typename OpD>
 static int residual_rows(const OpD& opd, long n, int S, int s_real, int nf, const c128* sigma, const c128* bint,
                          const c128* X, const c128* rs, int mode, c128* rpart, c128* rrow, hipStream_t st) {
-  const int Gr = resid_grid(n);
-  if (S >= 4) {
+  int Gr = resid_grid(n);
+  if constexpr (OpD::NB > 0) {
+    constexpr int JR = 4;
+    Gr = std::min(Gr, resid_fv_tiles(opd));   // no block without a tile
+    const dim3 gf(Gr, (nf + JR - 1) / JR, s_real);
+    if (mode == 0) k_resid_fv<OpD, JR, 0><<<gf, BS, 0, st>>>(opd, S, nf, sigma, bint, X, rs, rpart);
+    else k_resid_fv<OpD, JR, 1><<<gf, BS, 0, st>>>(opd, S, nf, sigma, bint, X, rs, rpart);
+  } else if (S >= 4) {
     constexpr int JR = 8;
     k_resid_jr<OpD, JR><<<dim3(Gr, (nf + JR - 1) / JR, s_real), BS, 0, st>>>(opd, n, S, nf, sigma, bint, X, rs, mode,
                                                                           rpart);
