@@ -900,8 +900,8 @@ __global__ void __launch_bounds__(BS * GSQ / Q) k_gs_update(long N, int S, int k
     n2[q] = t < N ? abs2(cvt<double>(ws)) : 0.0;
     s += n2[q];
   }
-  if constexpr (Q == 1) {
   if (!with_norm) return;
+  if constexpr (Q == 1) {
     __shared__ double sh[BT];
     sh[threadIdx.x] = s;
     __syncthreads();
