@@ -45,38 +45,35 @@ template <typename T> __device__ __forceinline__ int mfma_row(int g, int v) {
 // per lane a product of the n x kc block Z_r of its basis columns and the
 // kc x nf block of its coefficients.  A wave computes 16 cells x 16 TN shifts
 // of one lane (TN output tiles, complex as four real products per step of 4
-// basis columns); a block's 4 waves take 4 adjacent lanes of one tile of 16
-// cells, and the blocks of the other lanes of that tile sit 8 block indices
-// apart, on the same XCD (workgroups go to the XCDs round-robin), so the
-// basis rows of a tile come into one L2 only.  Z is read once per 16 TN
-// shifts and X written once.  FP64 accumulation (the order over the basis
-// columns is the matrix core's).
+// basis columns); a block's 4 waves take 4 tiles of 16 cells and share the
+// coefficients of their lane and shifts in LDS, ASM_KC columns at a time.  The
+// blocks of the other lanes of those cells sit 8 block indices apart, on the
+// same XCD (workgroups go to the XCDs round-robin), so the basis rows of a tile
+// come into one L2 only.  Z is read once per 16 TN shifts, a step ahead, and X
+// written once; the shifts are the rows of a tile and the cells its columns, so
+// that a store covers 16 adjacent cells (256 bytes) of a shift.  FP64
+// accumulation (the order over the basis columns is the matrix core's).
+// Bound by the writes of X (153 us at the rate of a copy for 262,144 cells and
+// 200 shifts) and the matrix products (145 us with 24 columns).  Those took 470
+// us with 64-byte stores and 64 shifts a wave, 410 with 256-byte stores, 350 with
+// the coefficients in LDS; 245 with 32 shifts a wave (TN = 2; 284 with TN = 1).
+constexpr int ASM_KC = 32;
 template <typename R, int TN>
-__global__ void __launch_bounds__(256) k_assemble_mfma(long n, int S, int s_real, int nf, int kc, int m,
+__global__ void __launch_bounds__(256, 4) k_assemble_mfma(long n, int S, int s_real, int nf, int kc, int m,
                                                        const cx<R>* __restrict__ Z, size_t cstride,
                                                        const c128* __restrict__ Yb,
                                                        const c128* __restrict__ ascale, c128* __restrict__ X,
                                                        int acc) {
+  constexpr int LD = 16 * TN + 1;
+  __shared__ c128 ys[ASM_KC * LD];   // [column][shift]
   const int lane = threadIdx.x & 63, g = lane >> 4, mm = lane & 15;
-  // block -> (tile of 16 cells, group of 4 lanes): groups of 8 tiles x LG lane
-  // groups, the tile's XCD slot fastest (fewer than 4 lanes: 4 / S tiles per
-  // block)
-  long tile;
-  int r;
-  if (S >= 4) {
-    const int LG = S >> 2;
-    const long b = blockIdx.x, per = 8L * LG;
-    const long grp = b / per;
-    const int rem = (int)(b - grp * per);
-    tile = grp * 8 + (rem & 7);
-    r = (rem >> 3) * 4 + (int)(threadIdx.x >> 6);
-  } else {
-    const long qq = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    tile = qq / S;
-    r = (int)(qq % S);
-  }
-  const long cell0 = tile * 16;
-  if (cell0 >= n || r >= s_real) return;   // whole waves
+  // block -> (64 cells, lane): groups of 8 tiles x S lanes, the tile's XCD slot
+  // fastest
+  const long per = 8L * S, grp = blockIdx.x / per;
+  const int rem = (int)(blockIdx.x - grp * per);
+  const int r = rem >> 3;
+  const long cell0 = ((grp * 8 + (rem & 7)) * 4 + (threadIdx.x >> 6)) * 16;
+  if (r >= s_real || cell0 - 16 * (int)(threadIdx.x >> 6) >= n) return;   // whole blocks
   const int j0 = (int)blockIdx.y * 16 * TN;
   d4m re[TN], im[TN];
 #pragma unroll
@@ -85,33 +82,42 @@ __global__ void __launch_bounds__(256) k_assemble_mfma(long n, int S, int s_real
     im[t] = d4m{0, 0, 0, 0};
   }
   const bool zin = cell0 + mm < n;
-  const size_t zc = (size_t)(cell0 + mm) * S + r;
-  for (int i0 = 0; i0 < kc; i0 += 4) {
-    const int i = i0 + g;
-    const bool iin = i < kc;
-    const c128 a = zin && iin ? cvt<double>(Z[(size_t)i * cstride + zc]) : c128{0.0, 0.0};
+  const cx<R>* zp = Z + (size_t)(zin ? cell0 + mm : 0) * S + r;
+  auto zload = [&](int i) { return zin && i < kc ? zp[(size_t)i * cstride] : cx<R>{0, 0}; };
+  cx<R> zn = zload(g);
+  for (int k0 = 0; k0 < kc; k0 += ASM_KC) {
+    const int kn = min(ASM_KC, kc - k0), kp = (kn + 3) & ~3;
+    if (k0 > 0) __syncthreads();   // the last columns' reads
+    for (int e = threadIdx.x; e < kp * 16 * TN; e += 256) {
+      const int i = e % kp, j = e / kp;
+      ys[i * LD + j] = i < kn && j0 + j < nf ? Yb[((size_t)(j0 + j) * S + r) * m + k0 + i] : c128{0.0, 0.0};
+    }
+    __syncthreads();
+    for (int i = 0; i < kp; i += 4) {
+      const c128 a = cvt<double>(zn);
+      zn = zload(k0 + i + 4 + g);
+      const c128* yr = ys + (i + g) * LD + mm;
 #pragma unroll
-    for (int t = 0; t < TN; ++t) {
-      const int j = j0 + 16 * t + mm;
-      const c128 y = iin && j < nf ? Yb[((size_t)j * S + r) * m + i] : c128{0.0, 0.0};
-      re[t] = mfma16(a.re, y.re, re[t]);
-      re[t] = mfma16(a.im, -y.im, re[t]);
-      im[t] = mfma16(a.re, y.im, im[t]);
-      im[t] = mfma16(a.im, y.re, im[t]);
+      for (int t = 0; t < TN; ++t) {
+        if (j0 + 16 * t >= nf) break;   // no shift in this tile
+        const c128 y = yr[16 * t];
+        re[t] = mfma16(y.re, a.re, re[t]);
+        re[t] = mfma16(-y.im, a.im, re[t]);
+        im[t] = mfma16(y.im, a.re, im[t]);
+        im[t] = mfma16(y.re, a.im, im[t]);
+      }
     }
   }
+  if (!zin) return;
 #pragma unroll
   for (int t = 0; t < TN; ++t) {
-    const int j = j0 + 16 * t + mm;
-    if (j >= nf) continue;
-    const c128 sc = ascale[(size_t)j * S + r];
-    c128* col = X + n * ((long)j + (long)nf * r);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const long cell = cell0 + mfma_row<double>(g, v);
-      if (cell >= n) continue;
-      const c128 val = sc * c128{re[t][v], im[t][v]};
-      col[cell] = acc ? col[cell] + val : val;
+      const int j = j0 + 16 * t + mfma_row<double>(g, v);
+      if (j >= nf) continue;
+      c128* dst = X + n * ((long)j + (long)nf * r) + cell0 + mm;
+      const c128 val = ascale[(size_t)j * S + r] * c128{re[t][v], im[t][v]};
+      *dst = acc ? *dst + val : val;
     }
   }
 }
@@ -143,16 +149,30 @@ __global__ void __launch_bounds__(64) k_blk_gram(const cx<TIn>* __restrict__ A, 
       im[a][b] = V4{0, 0, 0, 0};
     }
   cx<TIn> av[TM], bv[TN];
-  auto load = [&](long c) {
+  // the next PF steps' operands: the two waves a SIMD has here do not cover a
+  // load by themselves (256 x 256 x 64 columns, 8 blocks, FP64: 560 us without, 460 with)
+  constexpr int PF = 2;
+  cx<TIn> ap[PF][TM], bp[PF][TN];
+  auto load = [&](long c, int d) {
     const long cell = c + g;
     const bool ok = cell < c1;
 #pragma unroll
-    for (int a = 0; a < TM; ++a) av[a] = ok ? Ai[cell * S + 16 * a + m] : cx<TIn>{0, 0};
+    for (int a = 0; a < TM; ++a) ap[d][a] = ok ? Ai[cell * S + 16 * a + m] : cx<TIn>{0, 0};
 #pragma unroll
-    for (int b = 0; b < TN; ++b) bv[b] = ok ? B[cell * S + 16 * (nb0 + b) + m] : cx<TIn>{0, 0};
+    for (int b = 0; b < TN; ++b) bp[d][b] = ok ? B[cell * S + 16 * (nb0 + b) + m] : cx<TIn>{0, 0};
   };
-  for (long c = c0; c < c1; c += 4) {
-    load(c);
+#pragma unroll
+  for (int d = 0; d < PF; ++d) load(c0 + 4 * d, d);
+  for (long cb = c0; cb < c1; cb += 4 * PF)
+#pragma unroll
+  for (int d = 0; d < PF; ++d) {
+    const long c = cb + 4 * d;
+    if (c >= c1) break;
+#pragma unroll
+    for (int a = 0; a < TM; ++a) av[a] = ap[d][a];
+#pragma unroll
+    for (int b = 0; b < TN; ++b) bv[b] = bp[d][b];
+    load(c + 4 * PF, d);
 #pragma unroll
     for (int a = 0; a < TM; ++a) {
       const TAcc ar = (TAcc)av[a].re, ai = (TAcc)av[a].im;

@@ -732,12 +732,12 @@ static void launch_assemble(long n, int S, int s_real, int nf, int kc, int m, co
                             c128* Yt = nullptr) {
   const long N = n * S;
   if (tn().asm_mfma) {
-    // matrix cores: a wave per (16 cells, lane, 64 shifts); with 4 lanes or
-    // more the tiles go in groups of 8 (one per XCD slot) x S/4 lane groups
-    const long tiles = (n + 15) / 16;
-    const long blocks = S >= 4 ? (tiles + 7) / 8 * 8 * (S / 4) : (tiles * S + 3) / 4;
-    const dim3 grid((unsigned)blocks, (unsigned)((nf + 63) / 64));
-    k_assemble_mfma<R, 4><<<grid, 256, 0, st>>>(n, S, s_real, nf, kc, m, Z, cstride, Yb, ascale, X, acc);
+    // matrix cores: a block per (64 cells, lane, 32 shifts), the cell tiles in
+    // groups of 8 (one per XCD slot) x S lanes
+    const long tiles = (n + 63) / 64;
+    const long blocks = (tiles + 7) / 8 * 8 * S;
+    const dim3 grid((unsigned)blocks, (unsigned)((nf + 31) / 32));
+    k_assemble_mfma<R, 2><<<grid, 256, 0, st>>>(n, S, s_real, nf, kc, m, Z, cstride, Yb, ascale, X, acc);
     return;
   }
   const size_t lds = (size_t)kc * JT * S * sizeof(c128);
