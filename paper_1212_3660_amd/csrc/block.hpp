@@ -198,28 +198,39 @@ __global__ void __launch_bounds__(64) k_blk_gram(const cx<TIn>* __restrict__ A, 
       }
 }
 
-// Sum of the chunk partials of nb blocks in chunk order (FP64), one thread per
-// entry: block i's S x S result goes to H + i*S + ldh*col ((row, col) of the
-// block, column-major with leading dimension ldh; add != 0 accumulates), and
+// Sum of the chunk partials of nb blocks (FP64): chunks q, q + 4, .. by one of
+// four threads per entry, eight loads in flight, the four sums added in a fixed
+// order (one thread per entry left 16 workgroups on the chip: 37 us for one block
+// of 64 columns, now 8).  Block i's S x S result goes to H + i*S + ldh*col ((row, col) of
+// the block, column-major with leading dimension ldh; add != 0 accumulates), and
 // rounded to R into Cc[i] (row-major [r][r'], the update kernel's operand).
+// Launch: 64 entries per block.
 template <typename TAcc, typename R>
 __global__ void __launch_bounds__(BS) k_blk_reduce(const cx<TAcc>* __restrict__ part, int nch, int S,
                                                    c128* __restrict__ H, int ldh, int add,
                                                    cx<R>* __restrict__ Cc) {
-  const int e = blockIdx.x * BS + threadIdx.x;
-  if (e >= S * S) return;
+  __shared__ c128 sh[4][64];
+  const int el = threadIdx.x & 63, st = threadIdx.x >> 6;
+  const int e = blockIdx.x * 64 + el;   // S S is a multiple of 64
   const int i = blockIdx.y;
   const cx<TAcc>* p = part + (size_t)i * nch * S * S + e;
-  c128 a0{0, 0}, a1{0, 0}, a2{0, 0}, a3{0, 0};
-  int q = 0;
-  for (; q + 4 <= nch; q += 4) {
-    a0 = a0 + cvt<double>(p[(size_t)q * S * S]);
-    a1 = a1 + cvt<double>(p[(size_t)(q + 1) * S * S]);
-    a2 = a2 + cvt<double>(p[(size_t)(q + 2) * S * S]);
-    a3 = a3 + cvt<double>(p[(size_t)(q + 3) * S * S]);
+  const int n4 = nch & ~3;
+  c128 a{0, 0};
+  int q = st;
+  for (; q + 28 < n4; q += 32) {
+    cx<TAcc> v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = p[(size_t)(q + 4 * u) * S * S];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) a = a + cvt<double>(v[u]);
   }
-  for (; q < nch; ++q) a0 = a0 + cvt<double>(p[(size_t)q * S * S]);
-  const c128 s = (a0 + a1) + (a2 + a3);
+  for (; q < n4; q += 4) a = a + cvt<double>(p[(size_t)q * S * S]);
+  if (st == 0)
+    for (q = n4; q < nch; ++q) a = a + cvt<double>(p[(size_t)q * S * S]);
+  sh[st][el] = a;
+  __syncthreads();
+  if (st != 0) return;
+  const c128 s = (sh[0][el] + sh[1][el]) + (sh[2][el] + sh[3][el]);
   const int r = e / S, rp = e - r * S;
   if (H) {
     c128* h = H + (size_t)i * S + r + (size_t)ldh * rp;
@@ -252,20 +263,32 @@ __global__ void __launch_bounds__(256) k_blk_update(const cx<TIn>* A, size_t ast
       re[a][b] = V4{0, 0, 0, 0};
       im[a][b] = V4{0, 0, 0, 0};
     }
+  // the rows of A of the next step of 16, loaded a step ahead (256 x 256 x 64
+  // columns, 8 blocks, FP64: 376 us without, 350 with)
+  cx<TIn> ap[TMC][4];
+  auto load = [&](int i, int r0) {
+    const cx<TIn>* Ai = A + (size_t)i * astride;
+#pragma unroll
+    for (int a = 0; a < TMC; ++a) {
+      const long cell = cw + 16 * a + m;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) ap[a][t] = cell < n ? Ai[cell * S + r0 + 4 * g + t] : cx<TIn>{0, 0};
+    }
+  };
+  if (nb > 0) load(0, 0);
   for (int i = 0; i < nb; ++i) {
     __syncthreads();
     const cx<TC>* ci = Cc + (size_t)i * S * S;
     for (int e = threadIdx.x; e < S * S; e += 256) sc[(e / S) * LD + (e % S)] = ci[e];
     __syncthreads();
-    const cx<TIn>* Ai = A + (size_t)i * astride;
     for (int r0 = 0; r0 < S; r0 += 16) {
       cx<TIn> av[TMC][4];
 #pragma unroll
-      for (int a = 0; a < TMC; ++a) {
-        const long cell = cw + 16 * a + m;
+      for (int a = 0; a < TMC; ++a)
 #pragma unroll
-        for (int t = 0; t < 4; ++t) av[a][t] = cell < n ? Ai[cell * S + r0 + 4 * g + t] : cx<TIn>{0, 0};
-      }
+        for (int t = 0; t < 4; ++t) av[a][t] = ap[a][t];
+      if (r0 + 16 < S) load(i, r0 + 16);
+      else if (i + 1 < nb) load(i + 1, 0);
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         const int r = r0 + 4 * g + t;
@@ -310,113 +333,109 @@ __global__ void __launch_bounds__(256) k_blk_update(const cx<TIn>* A, size_t ast
 // is then zero).  Writes Rinv = R^{-1} (row-major, rounded to R) for the
 // update kernel, and Rout = R Rprev (column-major into H with leading
 // dimension ldh; Rprev row-major, or none).  Also ||Rout||_F^2 into *fro.
+//
+// One workgroup, bound by its chain of 64 steps, so a step is one barrier: every
+// thread takes the pivot's root itself and scales the entries of row q it needs
+// as it reads them (the scaled row goes to the other matrix, where nobody reads
+// it yet).  R^{-1} by columns, a wave per column: lane p holds row p, x_q is
+// broadcast from lane q and every row above subtracts R_pq x_q, with no barrier.
+// 64 columns: 234 us with three barriers a step and a thread per column of
+// R^{-1}, now 115 us.
+constexpr int CHOL_T = 1024;
 template <typename R>
-__global__ void __launch_bounds__(256) k_blk_chol(const c128* __restrict__ G, int S, const c128* __restrict__ Rprev,
-                                                  c128* __restrict__ Rout, int ldh, c128* __restrict__ Rrow,
-                                                  cx<R>* __restrict__ Rinv, double* __restrict__ fro) {
+__global__ void __launch_bounds__(CHOL_T) k_blk_chol(const c128* __restrict__ G, int S,
+                                                     const c128* __restrict__ Rprev, c128* __restrict__ Rout,
+                                                     int ldh, c128* __restrict__ Rrow, cx<R>* __restrict__ Rinv,
+                                                     double* __restrict__ fro) {
   extern __shared__ unsigned char blk_lds[];
-  c128* A = reinterpret_cast<c128*>(blk_lds);        // [S][S] row-major working copy, then R
-  c128* X = A + S * S;                                // [S][S] R^{-1}, then Rprev
+  const int LD = S + 1;
+  c128* A = reinterpret_cast<c128*>(blk_lds);        // [S][LD] row-major working copy, then Rprev
+  c128* T = A + S * LD;                               // [S][LD] R
   __shared__ double dmax;
-  __shared__ int dead[64];
-  __shared__ c128 rdi[64];                            // 1 / R_qq (0 for a dependent column)
+  __shared__ double rdi[64];                          // 1 / R_qq (0 for a dependent column)
+  __shared__ double fsum[CHOL_T / WAVE];
   const int t = threadIdx.x;
-  // thread t: column jc = t % 64, row group rg = t / 64 (rows rg, rg + 4, ...)
+  // thread t: column jc = t % 64, row group rg = t / 64 (one wave)
   const int jc = t & 63, rg = t >> 6;
-  for (int e = t; e < S * S; e += 256) A[e] = G[(e % S) * S + e / S];   // G column-major -> row-major
-  if (t < 64) dead[t] = 0;
+  constexpr int RG = CHOL_T / 64;
+  for (int e = t; e < S * S; e += CHOL_T) {   // G column-major -> row-major
+    A[(e / S) * LD + e % S] = G[(e % S) * S + e / S];
+    T[(e / S) * LD + e % S] = c128{0.0, 0.0};
+  }
   __syncthreads();
-  if (t == 0) {
-    double mx = 0.0;
-    for (int q = 0; q < S; ++q) mx = fmax(mx, A[q * S + q].re);
-    dmax = mx;
+  if (t < 64) {
+    double mx = t < S ? A[t * LD + t].re : 0.0;
+    mx = mx > 0.0 ? mx : 0.0;
+    for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, shfl_xor(mx, off));
+    if (t == 0) dmax = mx;
   }
   __syncthreads();
   for (int q = 0; q < S; ++q) {
-    const double d = A[q * S + q].re;
+    const double d = A[q * LD + q].re;
     const bool gone = !(d > 1e-26 * dmax);
     const double rq = gone ? 0.0 : sqrt(d);
     const double iq = gone ? 0.0 : 1.0 / rq;
-    __syncthreads();
-    // row q of R: R_qq = sqrt(d), R_qj = A_qj / R_qq (zero for a dependent column)
-    if (rg == 0 && jc >= q && jc < S) A[q * S + jc] = jc == q ? c128{rq, 0.0} : iq * A[q * S + jc];
-    if (t == 0) {
-      dead[q] = gone ? 1 : 0;
-      rdi[q] = c128{iq, 0.0};
-    }
-    __syncthreads();
-    // trailing update of the upper triangle: A_ij -= conj(R_qi) R_qj, q < i <= j
-    if (jc > q && jc < S) {
-      const c128 rj = A[q * S + jc];
-      for (int i = q + 1 + rg; i <= jc; i += 4) A[i * S + jc] = A[i * S + jc] - conj(A[q * S + i]) * rj;
+    if (jc >= q && jc < S) {
+      // row q of R: R_qq = sqrt(d), R_qj = A_qj / R_qq (zero for a dependent column)
+      const c128 rj = iq * A[q * LD + jc];
+      if (rg == 0) T[q * LD + jc] = jc == q ? c128{rq, 0.0} : rj;
+      if (rg == 0 && jc == q) rdi[q] = iq;
+      // trailing update of the upper triangle: A_ij -= conj(R_qi) R_qj, q < i <= j
+      for (int i = q + 1 + rg; i <= jc; i += RG)
+        A[i * LD + jc] = A[i * LD + jc] - conj(iq * A[q * LD + i]) * rj;
     }
     __syncthreads();
   }
-  // R^{-1}: column jc by the thread group of rg == 0 (rows upwards, four
-  // independent partial sums per row)
-  if (rg == 0 && jc < S) {
-    for (int i = 0; i < S; ++i) X[i * S + jc] = c128{0.0, 0.0};
-    if (!dead[jc]) {
-      X[jc * S + jc] = rdi[jc];
-      for (int i = jc - 1; i >= 0; --i) {
-        if (dead[i]) continue;
-        c128 s0{0, 0}, s1{0, 0}, s2{0, 0}, s3{0, 0};
-        int p = i + 1;
-        for (; p + 3 <= jc; p += 4) {
-          s0 = s0 + A[i * S + p] * X[p * S + jc];
-          s1 = s1 + A[i * S + p + 1] * X[(p + 1) * S + jc];
-          s2 = s2 + A[i * S + p + 2] * X[(p + 2) * S + jc];
-          s3 = s3 + A[i * S + p + 3] * X[(p + 3) * S + jc];
-        }
-        for (; p <= jc; ++p) s0 = s0 + A[i * S + p] * X[p * S + jc];
-        const c128 sum = (s0 + s1) + (s2 + s3);
-        X[i * S + jc] = -(rdi[i].re * sum);      // R_ii real positive
-      }
+  // R^{-1}: wave rg takes the columns rg, rg + RG, .. ; lane p holds row p
+  for (int c = rg; c < S; c += RG) {
+    const bool dead = rdi[c] == 0.0;
+    // acc_p = (unit vector - sum over the rows below of R_pq x_q)_p
+    c128 acc{jc == c && !dead ? 1.0 : 0.0, 0.0}, x{0.0, 0.0};
+    const int row = jc < S ? jc : 0;
+    c128 tq = T[row * LD + c];
+    for (int q = c; q >= 0; --q) {
+      const c128 tn = T[row * LD + (q > 0 ? q - 1 : 0)];   // ahead of the chain
+      if (jc == q) x = rdi[q] * acc;   // zero in the row of a dependent column
+      const c128 xq{readlane_f64(x.re, q), readlane_f64(x.im, q)};
+      if (jc < q) acc = acc - tq * xq;
+      tq = tn;
     }
+    if (jc < S) Rinv[jc * S + c] = cvt<R>(x);
   }
-  __syncthreads();
-  for (int e = t; e < S * S; e += 256) {
-    const int i = e / S, j = e % S;
-    Rinv[e] = cvt<R>(j >= i ? X[e] : c128{0.0, 0.0});
-  }
-  // Rout = R Rprev (both upper triangular), Rprev staged in X's space
-  __syncthreads();
+  // Rout = R Rprev (both upper triangular), Rprev staged in A's space
   if (Rprev)
-    for (int e = t; e < S * S; e += 256) X[e] = Rprev[e];
+    for (int e = t; e < S * S; e += CHOL_T) A[(e / S) * LD + e % S] = Rprev[e];
   __syncthreads();
-  __shared__ double fsum[256];
   double f = 0.0;
   if (jc < S) {
-    for (int i = rg; i <= jc; i += 4) {
-      c128 sv{0.0, 0.0};
-      if (Rprev) {
-        c128 s0{0, 0}, s1{0, 0};
-        int p = i;
-        for (; p + 1 <= jc; p += 2) {
-          s0 = s0 + A[i * S + p] * X[p * S + jc];
-          s1 = s1 + A[i * S + p + 1] * X[(p + 1) * S + jc];
+    for (int i = rg; i < S; i += RG) {
+      c128 sv{0.0, 0.0};   // zero below the diagonal
+      if (i <= jc) {
+        if (Rprev) {
+          c128 s4[4] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
+          int p = i;
+          for (; p + 3 <= jc; p += 4) {
+#pragma unroll
+            for (int w = 0; w < 4; ++w) s4[w] = s4[w] + T[i * LD + p + w] * A[(p + w) * LD + jc];
+          }
+          for (; p <= jc; ++p) s4[0] = s4[0] + T[i * LD + p] * A[p * LD + jc];
+          sv = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+        } else {
+          sv = T[i * LD + jc];
         }
-        for (; p <= jc; ++p) s0 = s0 + A[i * S + p] * X[p * S + jc];
-        sv = s0 + s1;
-      } else {
-        sv = A[i * S + jc];
       }
       if (Rout) Rout[i + (size_t)ldh * jc] = sv;
       if (Rrow) Rrow[i * S + jc] = sv;
       f += abs2(sv);
     }
-    // entries below the diagonal are zero
-    for (int i = jc + 1 + ((rg - (jc + 1) % 4 + 4) % 4); i < S; i += 4) {
-      if (Rout) Rout[i + (size_t)ldh * jc] = c128{0.0, 0.0};
-      if (Rrow) Rrow[i * S + jc] = c128{0.0, 0.0};
-    }
   }
-  fsum[t] = f;
+  f = wave_sum_strided(f, 1);
+  if (jc == 0) fsum[rg] = f;
   __syncthreads();
-  if (t == 0) {
+  if (t == 0 && fro) {
     double a = 0.0;
-    for (int q = 0; q < 256; ++q) a += fsum[q];
-    if (fro) *fro = a;
+    for (int q = 0; q < RG; ++q) a += fsum[q];
+    *fro = a;
   }
 }
 

@@ -1036,7 +1036,7 @@ template <typename R> struct BlkCtx {
     auto* part = reinterpret_cast<cx<TAcc>*>(gpart);
     k_blk_gram<TIn, TAcc, TM, TN><<<dim3((unsigned)nch, (unsigned)nb, ZG), 64, 0, st>>>(A, astride, Bm, n, (int)ch,
                                                                                        part);
-    k_blk_reduce<TAcc, R><<<dim3((unsigned)((S * S + BS - 1) / BS), (unsigned)nb), BS, 0, st>>>(part, (int)nch, S,
+    k_blk_reduce<TAcc, R><<<dim3((unsigned)(S * S / 64), (unsigned)nb), BS, 0, st>>>(part, (int)nch, S,
                                                                                                  Hcol, ldh, add, C);
   }
   template <typename TIn, typename TAcc>
@@ -1076,13 +1076,13 @@ template <typename R> struct BlkCtx {
   // R2 R1 goes to Rout (column-major, leading dimension ldh; may be null) and
   // row-major to Rrow_out (may be null); ||R||_F^2 to fro.
   template <typename TIn> void qr(const cx<TIn>* W, cx<R>* Vout, c128* Rout, int ldh, c128* Rrow_out) const {
-    const size_t lds = 2 * (size_t)S * S * sizeof(c128);
+    const size_t lds = 2 * (size_t)S * (S + 1) * sizeof(c128);
     cx<TIn>* rinv1 = reinterpret_cast<cx<TIn>*>(std::is_same<TIn, double>::value ? (void*)Rinv64 : (void*)Rinv);
     project<TIn, double>(W, 0, 1, W, Gm, S, 0, nullptr);
-    k_blk_chol<TIn><<<1, 256, lds, st>>>(Gm, S, nullptr, nullptr, 0, Rrow, rinv1, nullptr);
+    k_blk_chol<TIn><<<1, CHOL_T, lds, st>>>(Gm, S, nullptr, nullptr, 0, Rrow, rinv1, nullptr);
     apply<TIn, TIn, R>(W, 0, 1, rinv1, nullptr, Vout, 0.0, 1.0);
     project<R, double>(Vout, 0, 1, Vout, Gm, S, 0, nullptr);
-    k_blk_chol<R><<<1, 256, lds, st>>>(Gm, S, Rrow, Rout, ldh, Rrow_out, Rinv, fro);
+    k_blk_chol<R><<<1, CHOL_T, lds, st>>>(Gm, S, Rrow, Rout, ldh, Rrow_out, Rinv, fro);
     apply<R, R, R>(Vout, 0, 1, Rinv, nullptr, Vout, 0.0, 1.0);
   }
 };
