@@ -31,6 +31,11 @@ __device__ __forceinline__ int xcd_tile(int b, int G) {
   if (G & 7) return b;
   return (b & 7) * (G >> 3) + (b >> 3);
 }
+// The same bands, each from its end.
+__device__ __forceinline__ int xcd_tile_rev(int b, int G) {
+  if (G & 7) return G - 1 - b;
+  return (b & 7) * (G >> 3) + (G >> 3) - 1 - (b >> 3);
+}
 
 // Grid-stride walk over the items (cell, lane chunk) of a stencil kernel,
 // chunks fastest (lC = log2 of the chunks per cell).  On a grid operator with

@@ -212,18 +212,25 @@ __device__ __forceinline__ cx<R> mg_up_cell(const Op& op, const LevelDims& f, co
 // [x gy/8, (x+1) gy/8) of every plane, walked plane after plane: the blocks an
 // XCD runs at once then span a few planes of its slab, whose planes before and
 // after are still in its L2 (a band of whole planes is too large for it).
-__device__ __forceinline__ void xcd_block3(int& bx, int& by, int& bz) {
+//
+// BACK: the same blocks, each XCD's from its last to its first.  The four large
+// launches of an iteration on several lanes (step, finest restriction, finest
+// prolongation, product) each stream more than the 256 MB Infinity Cache holds,
+// so one that walks the way its predecessor did finds nothing of it there; the
+// step and the prolongations walk backwards, and each launch starts on what the
+// one before it touched last.
+template <bool BACK = false> __device__ __forceinline__ void xcd_block3(int& bx, int& by, int& bz) {
   const int gx = gridDim.x, gy = gridDim.y;
   const int w = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
   if (gridDim.z > 1 && (gy & 7) == 0) {
-    const int ry = gy >> 3, u = w >> 3;
+    const int ry = gy >> 3, n8 = gx * ry * gridDim.z, u = BACK ? n8 - 1 - (w >> 3) : w >> 3;
     bx = u % gx;
     const int r = u / gx;
     by = (w & 7) * ry + r % ry;
     bz = r / ry;
     return;
   }
-  const int T = xcd_tile(w, gx * gy * gridDim.z);
+  const int T = BACK ? xcd_tile_rev(w, gx * gy * gridDim.z) : xcd_tile(w, gx * gy * gridDim.z);
   const int r = T / gx;
   bx = T - r * gx;
   by = r % gy;
@@ -390,7 +397,7 @@ __global__ void __launch_bounds__(BS) k_mg_up_lanes(Op op, LevelDims f, LevelDim
   constexpr int NB = Op::NB;
   int flag = *all_done;
   int bx, j, k;
-  xcd_block3(bx, j, k);
+  xcd_block3<true>(bx, j, k);
   const int t = bx * BS + threadIdx.x;
   if (t >= (f.nx << lNC)) return;
   const int lc = t & ((1 << lNC) - 1), i = t >> lNC;
@@ -473,7 +480,7 @@ __global__ void __launch_bounds__(BS) k_mg_leg_rows(Op op, LevelDims f, LevelDim
   const int flag = *all_done;
   const int NC = 1 << lNC, S = 1 << lS, SW = BS >> lNC;
   const int nseg = (f.nx + SW - 1) / SW;
-  const int tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int tile = UP ? xcd_tile_rev(blockIdx.x, gridDim.x) : xcd_tile(blockIdx.x, gridDim.x);
   const int seg = tile % nseg, rb = tile / nseg;
   const int lc = (int)threadIdx.x & (NC - 1), ci = (int)threadIdx.x >> lNC;
   const int i = seg * SW + ci;
@@ -937,7 +944,7 @@ __global__ void __launch_bounds__(T3T) k_mg_leg_tile3(Op op, LevelDims f, LevelD
   __shared__ cx<R> stg[UP ? 1 : T3Y][UP ? 1 : T3X][LT];   // restriction: the children's sums
   const int flag = *all_done;
   int bxc, by, bz;
-  xcd_block3(bxc, by, bz);
+  xcd_block3<UP>(bxc, by, bz);
   const int ch = bxc % C, bx = bxc / C;
   if (!chunk_live<LT>(sc, ch * LT)) return;   // the block's chunk has stopped (uniform)
   const int tx = (int)threadIdx.x % T3X, ty = (int)threadIdx.x / T3X;
@@ -1927,8 +1934,10 @@ __global__ void __launch_bounds__(CGB) k_cgmg_step(OpD opd, c128 tau, int n, int
   XPlan xp;
   if (!cg_prologue<CGB, ONE>(lS, cfg, partIn, Gin, scIn, scOut, all_done, s, xp, par, blockIdx.x == 0)) return;
   auto for_cells = [&](auto&& f) {
-    if constexpr (MULTI) {
-      for (int t = t0; t < N; t += gridDim.x * CGB) f(t);
+    if constexpr (MULTI) {   // from the end (xcd_block3)
+      const int stride = gridDim.x * CGB;
+      if (t0 < N)
+        for (int t = t0 + (N - 1 - t0) / stride * stride; t >= t0; t -= stride) f(t);
     } else {
       if (t0 < N) f(t0);
     }
