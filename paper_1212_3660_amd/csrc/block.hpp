@@ -116,7 +116,7 @@ __global__ void __launch_bounds__(256, 4) k_assemble_mfma(long n, int S, int s_r
       const int j = j0 + 16 * t + mfma_row<double>(g, v);
       if (j >= nf) continue;
       c128* dst = X + n * ((long)j + (long)nf * r) + cell0 + mm;
-      const c128 val = ascale[(size_t)j * S + r] * c128{re[t][v], im[t][v]};
+      const c128 val = asm_scale(ascale, (size_t)j * S + r) * c128{re[t][v], im[t][v]};
       *dst = acc ? *dst + val : val;
     }
   }

@@ -921,14 +921,14 @@ __global__ void __launch_bounds__(BS * GSQ / Q) k_gs_update(long N, int S, int k
 }
 
 // v_{k+1} = w / h_{k+1,k}; lanes that broke down (h <= 1e-14 ||M z||, section
-// 3) or carry no rhs get a zero column.
+// 3; mz null: only h = 0) or carry no rhs get a zero column.
 template <typename R>
 __global__ void __launch_bounds__(BS) k_scale_col(long N, int S, const cx<R>* __restrict__ w,
                                                   const double* __restrict__ hn, const double* __restrict__ mz,
                                                   cx<R>* __restrict__ vout) {
   const int r = threadIdx.x & (S - 1);
   const double h = hn[r];
-  const bool ok = h > 1e-14 * mz[r] && h > 0.0;
+  const bool ok = h > 1e-14 * (mz ? mz[r] : 1e-300) && h > 0.0;
   const R inv = ok ? (R)(1.0 / h) : (R)0;
   for (long t = blockIdx.x * (long)BS + threadIdx.x; t < N; t += (long)gridDim.x * BS) vout[t] = inv * w[t];
 }
@@ -1458,6 +1458,11 @@ __global__ void __launch_bounds__(BS) k_gather_rows(const c128* __restrict__ X, 
 }
 
 // ------------------------------------------------------------ assembly -----
+// Multiplier of entry e of the assembly (no array: one).
+__device__ __forceinline__ c128 asm_scale(const c128* ascale, size_t e) {
+  return ascale ? ascale[e] : c128{1.0, 0.0};
+}
+
 // X[:, j, r] (+)= scale_j * Z_r y_{j,r} (Algorithm 4, x = Z y), FP64
 // accumulation.  Thread per item (cell, lane), JT shifts per block row.
 constexpr int JT = 16;
@@ -1487,7 +1492,7 @@ __global__ void __launch_bounds__(BS) k_assemble(long n, int S, int s_real, int 
     for (int q = 0; q < JT; ++q) {
       const int j = j0 + q;
       if (j < nf) {
-        const c128 v = ascale[(size_t)j * S + r] * acc[q];
+        const c128 v = asm_scale(ascale, (size_t)j * S + r) * acc[q];
         c128* dst = X + c + n * ((long)j + (long)nf * r);
         *dst = accumulate ? *dst + v : v;
       }
@@ -1547,7 +1552,7 @@ __global__ void __launch_bounds__(BS) k_assemble_rb(long n, int S, int lS, int s
     for (int q = 0; q < JQ; ++q) {
       const int j = j0 + q;
       if (j >= nf) break;
-      const c128 sc = ascale[(size_t)j * S + r];
+      const c128 sc = asm_scale(ascale, (size_t)j * S + r);
       c128* col = X + n * ((long)j + (long)nf * r);
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) {
@@ -1605,7 +1610,7 @@ __global__ void __launch_bounds__(BS) k_assemble_lds(long n, int S, int s_real, 
     for (int q = 0; q < JT; ++q) {
       const int j = j0 + q;
       if (j >= nf) break;
-      const c128 sc = ascale[(size_t)j * S + r];
+      const c128 sc = asm_scale(ascale, (size_t)j * S + r);
       const long off = n * ((long)j + (long)nf * r);
       if (h0) {
         c128* d = X + c0 + off;

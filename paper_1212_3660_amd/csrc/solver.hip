@@ -71,6 +71,94 @@ struct Pinned {
 };
 static thread_local Pinned g_pinned;
 
+// Device scratch of the step-level calls.  An allocation and its release cost
+// those calls 50 to 300 us, so blocks are kept for the next call: at most
+// SCRATCH_BLOCKS blocks of SCRATCH_BYTES in all, larger ones are not kept.  A
+// block comes back only from a call that has waited for its stream (idle), so
+// any thread and stream may take it; the blocks are freed when the last problem
+// is destroyed and when the device runs out of memory.
+constexpr int SCRATCH_BLOCKS = 8;
+constexpr size_t SCRATCH_BYTES = size_t(256) << 20;
+struct ScratchPool {
+  struct Block { void* p; size_t bytes; int dev; };
+  std::mutex mu;
+  std::vector<Block> blocks;   // oldest first
+  size_t held = 0;
+  int problems = 0;
+  void drop(size_t i) {
+    (void)hipFree(blocks[i].p);
+    held -= blocks[i].bytes;
+    blocks.erase(blocks.begin() + (long)i);
+  }
+  void trim() {
+    std::lock_guard<std::mutex> g(mu);
+    while (!blocks.empty()) drop(0);
+  }
+  hipError_t take(size_t bytes, void** p, size_t* got, int* dev) {
+    hipError_t e = hipGetDevice(dev);
+    if (e != hipSuccess) return e;
+    {
+      std::lock_guard<std::mutex> g(mu);
+      size_t best = blocks.size();
+      for (size_t i = 0; i < blocks.size(); ++i)
+        if (blocks[i].dev == *dev && blocks[i].bytes >= bytes && blocks[i].bytes <= 4 * bytes + (size_t(1) << 20) &&
+            (best == blocks.size() || blocks[i].bytes < blocks[best].bytes))
+          best = i;
+      if (best < blocks.size()) {
+        *p = blocks[best].p;
+        *got = blocks[best].bytes;
+        held -= blocks[best].bytes;
+        blocks.erase(blocks.begin() + (long)best);
+        return hipSuccess;
+      }
+    }
+    *got = bytes;
+    e = hipMalloc(p, bytes);
+    if (e == hipSuccess) return e;
+    (void)hipGetLastError();
+    trim();
+    return hipMalloc(p, bytes);
+  }
+  void put(void* p, size_t bytes, int dev) {
+    std::lock_guard<std::mutex> g(mu);
+    if (bytes > SCRATCH_BYTES) {
+      (void)hipFree(p);
+      return;
+    }
+    while (!blocks.empty() && ((int)blocks.size() >= SCRATCH_BLOCKS || held + bytes > SCRATCH_BYTES)) drop(0);
+    blocks.push_back({p, bytes, dev});
+    held += bytes;
+  }
+  void problem_up() {
+    std::lock_guard<std::mutex> g(mu);
+    ++problems;
+  }
+  void problem_down() {
+    bool last;
+    {
+      std::lock_guard<std::mutex> g(mu);
+      last = --problems == 0;
+    }
+    if (last) trim();
+  }
+};
+static ScratchPool& scratch_pool() {
+  static ScratchPool* pool = new ScratchPool;   // never destroyed: the runtime may be gone by then
+  return *pool;
+}
+struct DevBuf {
+  void* p = nullptr;
+  size_t bytes = 0;
+  int dev = 0;
+  bool idle = false;   // the work that used the block has been waited for
+  hipError_t take(size_t n) { return scratch_pool().take(n, &p, &bytes, &dev); }
+  ~DevBuf() {
+    if (!p) return;
+    if (idle) scratch_pool().put(p, bytes, dev);
+    else (void)hipFree(p);
+  }
+};
+
 // Inner-iteration kernel timing (shk_profile_*).
 struct KernelTimer {
   bool on = false;
@@ -175,6 +263,10 @@ static hipError_t dev_alloc(shk_problem* p, void** ptr, size_t bytes, hipStream_
 }
 
 void problem_free(shk_problem* p, hipStream_t st) {
+  if (p->counted) {
+    p->counted = false;
+    scratch_pool().problem_down();
+  }
   if (p->bump) {   // the region's owner releases it as a whole
     p->mg.clear();
     return;
@@ -304,6 +396,8 @@ int problem_setup_fv(shk_problem* p, const double* K, double Ss, double h, hipSt
   p->cellK = Kd;   // kept for sensitivities
   SHK_TRY(mg_setup(p, st));
   SHK_HIP(hipStreamSynchronize(st));
+  p->counted = true;
+  scratch_pool().problem_up();
   return SHK_OK;
 }
 
@@ -346,6 +440,8 @@ int problem_setup_csr(shk_problem* p, const int* rowptr, const int* col, const d
   SHK_HIP(hipMemcpyAsync(p->dK, dg.data(), n * sizeof(double), hipMemcpyHostToDevice, st));
   SHK_HIP(hipMemcpyAsync(p->dK32, dg32.data(), n * sizeof(float), hipMemcpyHostToDevice, st));
   SHK_HIP(hipStreamSynchronize(st));
+  p->counted = true;
+  scratch_pool().problem_up();
   return SHK_OK;
 }
 
@@ -2426,13 +2522,6 @@ int solve_all(shk_problem* p, const shk_params* prm, int nf, const c128* sigma, 
 }
 
 // ---------------------------------------------------------- step level -----
-struct DevBuf {
-  void* p = nullptr;
-  ~DevBuf() {
-    if (p) (void)hipFree(p);
-  }
-};
-
 int step_apply(shk_problem* p, c128 sigma, int S, const void* x, void* y, int precision, hipStream_t st) {
   if (!p || !x || !y || S < 1 || S > 64 || (S & (S - 1))) return fail(SHK_ERR_INVALID_ARG, "apply arguments");
   const long N = p->n * S;
@@ -2485,7 +2574,7 @@ int step_inner(shk_problem* p, c128 tau, int S, const void* v, void* z, void* w,
     Buffers<R> b0{};
     lay(cv, b0);
     DevBuf mem;
-    SHK_HIP(hipMalloc(&mem.p, cv.off));
+    SHK_HIP(mem.take(cv.off));
     SHK_HIP(hipMemsetAsync(mem.p, 0, cv.off, st));
     Carver c2{(char*)mem.p};
     Buffers<R> b{};
@@ -2502,8 +2591,11 @@ int step_inner(shk_problem* p, c128 tau, int S, const void* v, void* z, void* w,
       }
       Snap* snap = (Snap*)g_pinned.get(65536);
       std::vector<double> pn(S);
-      SHK_HIP(hipMemcpyAsync(pn.data(), b.pn, sizeof(double) * S, hipMemcpyDeviceToHost, st));
+      double* pnh = (double*)((char*)snap + 32768);
+      SHK_HIP(hipMemcpyAsync(pnh, b.pn, sizeof(double) * S, hipMemcpyDeviceToHost, st));
       SHK_HIP(hipStreamSynchronize(st));
+      mem.idle = true;
+      std::copy(pnh, pnh + S, pn.begin());
       for (int r = 0; r < S; ++r) {
         if (its) its[r] = snap->sc[r].its;
         if (pnorm) pnorm[r] = pn[r];
@@ -2526,28 +2618,28 @@ int step_orth(long long n, int S, int k, void* V, void* w, c128* h, int precisio
     auto lay = [&](Carver& c, Buffers<R>& b) {
       b.part = c.take<c128>(std::max<size_t>((size_t)Gd * (k + 1) * S, (size_t)Gu * S));
       b.H = c.take<c128>((size_t)(k + 2) * S); b.h2 = c.take<c128>((size_t)(k + 1) * S);
-      b.hn = c.take<double>(S); b.mz = c.take<double>(S);
+      b.hn = c.take<double>(S);
     };
     Carver cv{nullptr};
     Buffers<R> b0{};
     lay(cv, b0);
     DevBuf mem;
-    SHK_HIP(hipMalloc(&mem.p, cv.off));
-    SHK_HIP(hipMemsetAsync(mem.p, 0, cv.off, st));
+    SHK_HIP(mem.take(cv.off));
     Carver c2{(char*)mem.p};
     Buffers<R> b{};
     lay(c2, b);
-    std::vector<double> tiny(S, 1e-300);
-    SHK_HIP(hipMemcpyAsync(b.mz, tiny.data(), sizeof(double) * S, hipMemcpyHostToDevice, st));
     cx<R>* Vp = (cx<R>*)V;
     const int kc = k;
     gram_schmidt<R>(N, S, kc, Vp, (cx<R>*)w, b.H, b.h2, b.part, ortho == SHK_MGS, st);
     launch_final_sqrt<1>(b.part, (int)Gu, S, b.hn, nullptr, b.H + (size_t)kc * S, st);
-    k_scale_col<R><<<grid_items(N, 4096), BS, 0, st>>>(N, S, (const cx<R>*)w, b.hn, b.mz, Vp + (size_t)kc * N);
+    k_scale_col<R><<<grid_items(N, 4096), BS, 0, st>>>(N, S, (const cx<R>*)w, b.hn, nullptr, Vp + (size_t)kc * N);
     SHK_HIP(hipGetLastError());
-    std::vector<c128> hh((size_t)(k + 1) * S);
-    SHK_HIP(hipMemcpyAsync(hh.data(), b.H, sizeof(c128) * (k + 1) * S, hipMemcpyDeviceToHost, st));
+    const size_t nh = (size_t)(k + 1) * S;
+    c128* hh = (c128*)g_pinned.get(std::max<size_t>(65536, nh * sizeof(c128)));
+    if (!hh) return fail(SHK_ERR_OOM, "pinned staging");
+    SHK_HIP(hipMemcpyAsync(hh, b.H, sizeof(c128) * nh, hipMemcpyDeviceToHost, st));
     SHK_HIP(hipStreamSynchronize(st));
+    mem.idle = true;
     for (int r = 0; r < S; ++r)
       for (int i = 0; i <= k; ++i) h[i + (size_t)(k + 1) * r] = hh[(size_t)i * S + r];
     return SHK_OK;
@@ -2575,7 +2667,7 @@ int step_block_orth(long long n, int S, int k, void* V, void* W, c128* h, int pr
     Buffers<R> b0{};
     lay(cv, b0);
     DevBuf mem;
-    SHK_HIP(hipMalloc(&mem.p, cv.off));
+    SHK_HIP(mem.take(cv.off));
     Carver c2{(char*)mem.p};
     Buffers<R> b{};
     lay(c2, b);
@@ -2586,6 +2678,7 @@ int step_block_orth(long long n, int S, int k, void* V, void* W, c128* h, int pr
     SHK_HIP(hipGetLastError());
     SHK_HIP(hipMemcpyAsync(h, b.Hb, sizeof(c128) * (size_t)ldh * S, hipMemcpyDeviceToHost, st));
     SHK_HIP(hipStreamSynchronize(st));
+    mem.idle = true;
     return SHK_OK;
   };
   return precision == SHK_MIXED ? run(float{}) : run(double{});
@@ -2611,7 +2704,7 @@ int step_block_lsq(int K, int S, const c128* H, const c128* taus, int nf, const 
   };
   lay(cv, b0);
   DevBuf mem;
-  SHK_HIP(hipMalloc(&mem.p, cv.off));
+  SHK_HIP(mem.take(cv.off));
   SHK_HIP(hipMemset(mem.p, 0, cv.off));
   Carver c2{(char*)mem.p};
   Buffers<double> b{};
@@ -2645,6 +2738,7 @@ int step_block_lsq(int K, int S, const c128* H, const c128* taus, int nf, const 
   blk_backsolve_launch(sa, S, nf, nullptr);
   SHK_HIP(hipGetLastError());
   SHK_HIP(hipMemcpy(y, b.Yp, sizeof(c128) * (size_t)L * mS, hipMemcpyDeviceToHost));
+  mem.idle = true;
   return SHK_OK;
 }
 
@@ -2664,7 +2758,7 @@ int step_lsq(int K, const c128* H, const c128* taus, int nf, const c128* sigma, 
   };
   lay(cv, b0);
   DevBuf mem;
-  SHK_HIP(hipMalloc(&mem.p, cv.off));
+  SHK_HIP(mem.take(cv.off));
   SHK_HIP(hipMemset(mem.p, 0, cv.off));
   Carver c2{(char*)mem.p};
   Buffers<double> b{};
@@ -2696,6 +2790,7 @@ int step_lsq(int K, const c128* H, const c128* taus, int nf, const c128* sigma, 
   }
   std::vector<c128> Y((size_t)L * m);
   SHK_HIP(hipMemcpy(Y.data(), b.Yb, sizeof(c128) * Y.size(), hipMemcpyDeviceToHost));
+  mem.idle = true;
   for (int j = 0; j < nf; ++j)
     for (int i = 0; i < K; ++i) y[i + (size_t)K * j] = Y[(size_t)j * m + i];
   return SHK_OK;
@@ -2704,13 +2799,9 @@ int step_lsq(int K, const c128* H, const c128* taus, int nf, const c128* sigma, 
 int step_assemble(long long n, int k, int nf, const void* Z, const c128* Y, c128* X, int acc, int precision,
                   hipStream_t st) {
   if (!Z || !Y || !X || k < 1 || nf < 1 || n < 1) return fail(SHK_ERR_INVALID_ARG, "assemble arguments");
-  DevBuf ones;
-  SHK_HIP(hipMalloc(&ones.p, sizeof(c128) * nf));
-  std::vector<c128> o(nf, c128{1.0, 0.0});
-  SHK_HIP(hipMemcpyAsync(ones.p, o.data(), sizeof(c128) * nf, hipMemcpyHostToDevice, st));
   auto run = [&](auto tag) -> int {
     using R = decltype(tag);
-    launch_assemble<R>((long)n, 1, 1, nf, k, k, (const cx<R>*)Z, (size_t)n, Y, (const c128*)ones.p, X, acc, st);
+    launch_assemble<R>((long)n, 1, 1, nf, k, k, (const cx<R>*)Z, (size_t)n, Y, nullptr, X, acc, st);
     SHK_HIP(hipGetLastError());
     SHK_HIP(hipStreamSynchronize(st));
     return SHK_OK;
@@ -2792,8 +2883,10 @@ int step_true_residual(shk_problem* p, int nf, const c128* sigma, const c128* b,
                        hipStream_t st) {
   SHK_TRY(check_resid_args(p, nf, sigma, b, x, relres));
   DevBuf mem;
-  SHK_HIP(hipMalloc(&mem.p, resid_scratch(nullptr, p->n, nf).bytes));
-  return true_residual_in(p, nf, sigma, b, x, relres, st, (char*)mem.p);
+  SHK_HIP(mem.take(resid_scratch(nullptr, p->n, nf).bytes));
+  const int rc = true_residual_in(p, nf, sigma, b, x, relres, st, (char*)mem.p);
+  mem.idle = rc == SHK_OK;   // it waits for the stream last
+  return rc;
 }
 
 // ------------------------------------------- allocation-free residual ------
