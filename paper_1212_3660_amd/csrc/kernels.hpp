@@ -631,6 +631,75 @@ __device__ __forceinline__ void cg_compute(const CgCell<Op, R>& L, int t, cx<R> 
   arr += abs2(rd);
 }
 
+// A CSR row's own vectors and its first CE entries with r, w, s and D^-1 at
+// their columns, all loaded before the prologue's sums are waited for: row
+// pointer, entries and gathers are three dependent round trips, which a row loop
+// after the prologue pays once for every entry (21,000 rows of five, complex128:
+// 8.4 -> 7.8 us a launch, an inner solve of 90 launches 900 -> 767 us with the
+// state's copy kept out of scratch memory).  The registers that hold it leave two
+// wavefronts a SIMD: up to CSR_ROW_WAVES of them, all resident at once, it is
+// the faster form (129,600 rows: 1334 -> 1218 us a solve); above, the loop is
+// (160,000 rows: held 1500, loop 1397 us).
+constexpr int CSR_ROW_WAVES = 2048;
+template <typename R> struct CsrRow {
+  static constexpr int CE = 6;
+  int e0, e1;
+  R v[CE];
+  cx<R> r[CE], w[CE], s[CE], d[CE];
+  cx<R> r_, w_, s_, d_, p_;  // the row's own
+  c128 x_;
+  R m_;
+  template <typename Op>
+  __device__ __forceinline__ void own(const Op& op, const cx<R>* __restrict__ dinv, int t, int c,
+                                      const cx<R>* __restrict__ r0, const cx<R>* __restrict__ w0,
+                                      const cx<R>* __restrict__ s0, const CgVecs<R>& vec) {
+    r_ = r0[t];
+    w_ = w0[t];
+    s_ = s0[t];
+    p_ = vec.p[t];
+    x_ = vec.x[t];
+    d_ = dinv[c];
+    m_ = (R)op.mass(c);
+  }
+  template <typename Op>
+  __device__ __forceinline__ void load(const Op& op, const cx<R>* __restrict__ dinv, int lS, int rl, int c,
+                                       const cx<R>* __restrict__ r0, const cx<R>* __restrict__ w0,
+                                       const cx<R>* __restrict__ s0, const CgVecs<R>& vec) {
+    e0 = e1 = 0;
+    if (c >= 0) {
+      e0 = op.rowptr[c];
+      e1 = op.rowptr[c + 1];
+      own(op, dinv, (c << lS) + rl, c, r0, w0, s0, vec);
+    }
+    int col[CE];
+#pragma unroll
+    for (int k = 0; k < CE; ++k) {
+      const bool in = e0 + k < e1;
+      col[k] = in ? op.col[e0 + k] : -1;
+      v[k] = in ? (R)op.val[e0 + k] : (R)0;
+    }
+#pragma unroll
+    for (int k = 0; k < CE; ++k) {
+      if (col[k] < 0) continue;
+      const int q = (col[k] << lS) + rl;
+      r[k] = r0[q];
+      w[k] = w0[q];
+      s[k] = s0[q];
+      d[k] = dinv[col[k]];
+    }
+  }
+  // (K + tau M) u' at the row; uc: u' there, gu: u' at any column
+  template <typename Op, typename G>
+  __device__ __forceinline__ cx<R> apply(const Op& op, cx<R> tr, cx<R> al, cx<R> be, cx<R> uc, G gu) const {
+    cx<R> acc = m_ * (tr * uc);
+#pragma unroll
+    for (int k = 0; k < CE; ++k)
+      if (e0 + k < e1) acc = acc + v[k] * ((r[k] - al * (w[k] + be * s[k])) * d[k]);
+    for (int e = e0 + CE; e < e1; ++e) acc = acc + (R)op.val[e] * gu(op.col[e]);
+    return acc;
+  }
+};
+
 // One launch of the inner solve for every lane: an iteration, or a step of a
 // round change on the complex64 path (see cg_advance).  Vectors alternate
 // between two buffers by launch parity (par, from the host): a lane that has
@@ -661,13 +730,16 @@ __global__ void __launch_bounds__(CGB) k_cg_step(Op op, OpD opd, const cx<R>* __
   PartLoad<3, KMAX> PL;
   part_load<3, KMAX, CGB>(partIn, Gin, S, PL);
   CgScal s = scIn[rl];
+  s.apend = c128{0.0, 0.0};  // only copied here: left alone it goes to scratch, behind a wait for every load
   const int N = n << lS;
-  const cx<R>* __restrict__ r0 = vec.r[par];
-  const cx<R>* __restrict__ w0 = vec.w[par];
-  const cx<R>* __restrict__ s0 = vec.s[par];
-  cx<R>* __restrict__ r1 = vec.r[par ^ 1];
-  cx<R>* __restrict__ w1 = vec.w[par ^ 1];
-  cx<R>* __restrict__ s1 = vec.s[par ^ 1];
+  // both buffers' pointers are read and one is taken: an indexed read would
+  // wait for the parity before it starts
+  const cx<R>* __restrict__ r0 = par ? vec.r[1] : vec.r[0];
+  const cx<R>* __restrict__ w0 = par ? vec.w[1] : vec.w[0];
+  const cx<R>* __restrict__ s0 = par ? vec.s[1] : vec.s[0];
+  cx<R>* __restrict__ r1 = par ? vec.r[0] : vec.r[1];
+  cx<R>* __restrict__ w1 = par ? vec.w[0] : vec.w[1];
+  cx<R>* __restrict__ s1 = par ? vec.s[0] : vec.s[1];
   const int t0 = xcd_tile(blockIdx.x, gridDim.x) * CGB + threadIdx.x;
   // the thread's cells: one, or a grid-stride loop when the grid is capped
   auto for_cells = [&](auto&& f) {
@@ -678,6 +750,8 @@ __global__ void __launch_bounds__(CGB) k_cg_step(Op op, OpD opd, const cx<R>* __
       if (t0 < N) f(t0);
     }
   };
+  CsrRow<R> row;
+  if constexpr (Op::NB == 0 && !MULTI) row.load(op, dinv, lS, rl, t0 < N ? t0 >> lS : -1, r0, w0, s0, vec);
   c128 tot[3];
   part_sum<3, KMAX, CGB>(partIn, Gin, S, PL, tot);
   if (flag) {
@@ -713,15 +787,16 @@ __global__ void __launch_bounds__(CGB) k_cg_step(Op op, OpD opd, const cx<R>* __
         };
         for_cells([&](int t) {
           const int c = t >> lS;
-          const cx<R> di = dinv[c];
-          const cx<R> rc = r0[t];
-          const cx<R> sn = w0[t] + be * s0[t];
-          const cx<R> rn = rc - al * sn;
-          const cx<R> pn = rc * di + be * vec.p[t];
+          if constexpr (MULTI) row.own(op, dinv, t, c, r0, w0, s0, vec);
+          const cx<R> sn = row.w_ + be * row.s_;
+          const cx<R> rn = row.r_ - al * sn;
+          const cx<R> pn = row.r_ * row.d_ + be * row.p_;
           vec.p[t] = pn;
-          vec.x[t] = vec.x[t] + al64 * cvt<double>(pn);
-          const cx<R> un = rn * di;
-          const cx<R> wn = op.template apply<R>(c, tr, gu);
+          vec.x[t] = row.x_ + al64 * cvt<double>(pn);
+          const cx<R> un = rn * row.d_;
+          cx<R> wn;
+          if constexpr (MULTI) wn = op.template apply<R>(c, tr, gu);
+          else wn = row.apply(op, tr, al, be, un, gu);
           r1[t] = rn;
           w1[t] = wn;
           s1[t] = sn;

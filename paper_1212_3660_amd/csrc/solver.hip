@@ -1204,7 +1204,9 @@ template <typename R, typename Op, typename OpD> struct Group {
   template <int CGB, bool NT>
   void step_nt(int G, c128 tau, int ni, int lS, const CgCfg& e, const c128* in, int Gin, const CgScal* scIn,
                CgScal* scOut, const CgVecs<R>& vec, int par, c128* out) {
-    const bool multi = (long)G * CGB < N;
+    // a general sparse K also takes the looping form (one cell a thread) above
+    // CSR_ROW_WAVES: the one that holds a row ahead keeps 2 wavefronts a SIMD
+    const bool multi = (long)G * CGB < N || (Op::NB == 0 && (long)G * CGB > 64L * CSR_ROW_WAVES);
     if (lS == 0) {
       if (multi) step_k<CGB, NT, true, true>(G, tau, ni, lS, e, in, Gin, scIn, scOut, vec, par, out);
       else step_k<CGB, NT, true, false>(G, tau, ni, lS, e, in, Gin, scIn, scOut, vec, par, out);
