@@ -908,7 +908,7 @@ __global__ void __launch_bounds__(BS) k_gs_dot(long N, int S, int kc, const cx<R
 
 // One block per (column i, lane r), entry e = i S + r: sum the partials over G
 // blocks.  The entries of a 128-byte line of the partials go to blocks of one
-// XCD (as in k_lane_totals): with 64 lanes and 21 columns 57 -> 14 us.
+// XCD (as in k_lane_totals): with 64 lanes and 21 columns 57 -> 21 us.
 __global__ void __launch_bounds__(BS) k_gs_reduce(const c128* __restrict__ part, int G, int kc, int S,
                                                   c128* __restrict__ main_out, c128* __restrict__ aux_out,
                                                   int accumulate) {
@@ -1769,7 +1769,7 @@ __global__ void __launch_bounds__(BS) k_resid_jr(Op op, long n, int S, int nf, c
 // planes before and after, mostly from the CU's L1; in 2-D they take four
 // adjacent row segments.  Tiles (planes, rows, segments, the last fastest) go
 // over the grid in XCD bands.  512 x 512 x 200 shifts: 397 us with a cell's five
-// values loaded at every cell and indices divided, now 190 us.
+// values loaded at every cell and indices divided, now 176 us.
 constexpr int RESID_YB = 16;
 template <typename Op> struct ResidTiles {   // tiles along x, y and z
   int x, y, z;
