@@ -311,7 +311,8 @@ template <int LT> __device__ __forceinline__ bool chunk_live(const CgScal* __res
 // lc LT .. lc LT + LT - 1; lNC = log2(S / LT).
 // Down: grid (ceil(c.nx 2^(lNC + d) / BS), c.ny, c.nz); the 2^d children of a
 // coarse cell and its chunks share a run of 2^(d + lNC) threads.
-template <typename Op, typename R, int LT>
+// PL: a lane's coarse right-hand side contiguous (see k_mg_tail2d).
+template <typename Op, typename R, int LT, bool PL>
 __global__ void __launch_bounds__(BS) k_mg_down_lanes(Op op, LevelDims f, LevelDims c, c128 tau, double omega,
                                                       int lS, int lNC, const cx<R>* __restrict__ b,
                                                       const cx<R>* __restrict__ dinv, cx<R>* __restrict__ out,
@@ -380,9 +381,11 @@ __global__ void __launch_bounds__(BS) k_mg_down_lanes(Op op, LevelDims f, LevelD
   }
   hold(v[0], flag);
   if (!flag && q == 0 && live) {
-    cx<R>* o = out + ((long)(I + c.nx * (J + c.ny * L)) << lS) + lc * LT;
+    const int cc = I + c.nx * (J + c.ny * L);
+    const long ls = PL ? (long)c.nx * c.ny * c.nz : 1;
+    cx<R>* o = out + (PL ? lc * LT * ls + cc : ((long)cc << lS) + lc * LT);
 #pragma unroll
-    for (int l = 0; l < LT; ++l) o[l] = v[l];
+    for (int l = 0; l < LT; ++l) o[l * ls] = v[l];
   }
 }
 
@@ -1607,12 +1610,17 @@ template <typename R> __device__ __forceinline__ void t2_pin(T2Cell<R>& c) {
   asm volatile("" : "+v"(c.fo[0]), "+v"(c.fo[1]), "+v"(c.fo[2]), "+v"(c.fo[3]));
 }
 
-// Workgroup g takes lane g of the 2^lSg that btop and xtop interleave.  nx, ny:
+// Workgroup g takes lane g of the 2^lSg that btop and xtop interleave.  btop may
+// hold the lanes one after another instead (planar), as the lane kernel of the
+// leg before then writes it: interleaved, each of 64 workgroups fetches every
+// sector for one of its lanes (256 x 256, 64 lanes: 20.1 -> 15.7 us).  xtop
+// stays interleaved: the leg after has a wave's threads over chunks of lanes and
+// took 14.6 us instead of 8.3 with planar input.  nx, ny:
 // the level of btop, the top level (TOP4) or the base level; J base levels.
 // lanes_order: the top level rounds as k_mg_down_lanes and k_mg_up_lanes do,
 // else as k_mg_down and k_mg_up.
 template <typename R, bool TOP4>
-__global__ void __launch_bounds__(MG_TAIL_THREADS) k_mg_tail2d(int nx, int ny, int J, int lanes_order,
+__global__ void __launch_bounds__(MG_TAIL_THREADS) k_mg_tail2d(int nx, int ny, int J, int lanes_order, int planar,
                                                                c128 tau, double omega, int lSg,
                                                                const R* __restrict__ pack,
                                                                const cx<R>* __restrict__ btop,
@@ -1622,6 +1630,8 @@ __global__ void __launch_bounds__(MG_TAIL_THREADS) k_mg_tail2d(int nx, int ny, i
   extern __shared__ __align__(16) char lds_raw[];
   cx<R>* sh = reinterpret_cast<cx<R>*>(lds_raw);
   constexpr int NT = TOP4 ? 4 : 1;
+  const int lg = planar ? 0 : lSg;
+  const long g0 = planar ? (long)blockIdx.x * nx * ny : blockIdx.x;
   const int flag = *all_done;
   const int stopped = lSg > 0 ? (int)sc[blockIdx.x].done : 0;
   const int t = threadIdx.x, lane = t & (WAVE - 1);
@@ -1657,7 +1667,7 @@ __global__ void __launch_bounds__(MG_TAIL_THREADS) k_mg_tail2d(int nx, int ny, i
   for (int q = 0; q < NT; ++q) {
     const int i = TOP4 ? 2 * X + (q & 1) : X, j = TOP4 ? 2 * Y + (q >> 1) : Y;
     const bool in = i < nx && j < ny;
-    const cx<R> v = btop[((long)(in ? i + nx * j : 0) << lSg) + blockIdx.x];
+    const cx<R> v = btop[((long)(in ? i + nx * j : 0) << lg) + g0];
     bt[q] = in ? v : cx<R>{0, 0};
   }
   T2Cell<R> cb0 = t2_load<R>(pack, 0, t);

@@ -1447,30 +1447,49 @@ template <typename R, typename Op, typename OpD> struct Group {
                                                                bl, dl, xcoarse, out, vsc, B.all_done);
     }
   }
+  // lanes of a chunk in the down leg's lane kernel, and whether a leg marches rows instead
+  int down_chunk(int lS) const { return std::min(c64 ? tn().down_lt : tn().lt64, 1 << lS); }
+  bool lanes_rows(const LevelDims& f, int lS, int lt) const {
+    return lt * sizeof(cx<R>) <= 32 && rows_for(f, lS - ilog2(lt));
+  }
+  // The tail's right-hand side with a lane's cells contiguous: the register tail
+  // under a leg of the lane kernel.
+  bool tail_planar(int t, int lS, int from) const {
+    if (Op::NB != 4 || lS == 0 || !lane_chunks() || t <= from || tail2d_level(lS) != t) return false;
+    return !lanes_rows(mg_dims(t - 1), lS, down_chunk(lS));
+  }
   template <int LT>
   void mg_down_lt(int l, const LevelDims& f, const LevelDims& c, c128 tau, int lS, const cx<R>* bl, const cx<R>* dl,
-                  cx<R>* out) {
+                  cx<R>* out, bool pl) {
     const int lNC = lS - ilog2(LT);
-    if (LT * sizeof(cx<R>) <= 32 && rows_for(f, lNC)) {
+    if (lanes_rows(f, lS, LT)) {
       leg_rows<false, LT>(l, f, c, tau, lS, lNC, bl, dl, nullptr, out);
       return;
     }
     const dim3 g((unsigned)((((long)c.nx << (lNC + Op::NB / 2)) + BS - 1) / BS), (unsigned)c.ny, (unsigned)c.nz);
-    k_mg_down_lanes<Op, R, LT><<<g, BS, 0, st>>>(mg_op<Op, R>(op, l), f, c, tau, mg_omega, lS, lNC, bl, dl, out,
-                                                 vsc, B.all_done);
+    auto go = [&](auto kern) {
+      kern<<<g, BS, 0, st>>>(mg_op<Op, R>(op, l), f, c, tau, mg_omega, lS, lNC, bl, dl, out, vsc, B.all_done);
+    };
+    if constexpr (Op::NB == 4) {
+      if (pl) {
+        go(k_mg_down_lanes<Op, R, LT, true>);
+        return;
+      }
+    }
+    go(k_mg_down_lanes<Op, R, LT, false>);
   }
   void mg_down_lanes(int l, const LevelDims& f, const LevelDims& c, c128 tau, int lS, const cx<R>* bl,
-                     const cx<R>* dl, cx<R>* out) {
-    const int lt = std::min(c64 ? tn().down_lt : tn().lt64, 1 << lS);
-    if (lt == 2) mg_down_lt<2>(l, f, c, tau, lS, bl, dl, out);
-    else if (lt == 4) mg_down_lt<4>(l, f, c, tau, lS, bl, dl, out);
-    else mg_down_lt<8>(l, f, c, tau, lS, bl, dl, out);
+                     const cx<R>* dl, cx<R>* out, bool pl) {
+    const int lt = down_chunk(lS);
+    if (lt == 2) mg_down_lt<2>(l, f, c, tau, lS, bl, dl, out, pl);
+    else if (lt == 4) mg_down_lt<4>(l, f, c, tau, lS, bl, dl, out, pl);
+    else mg_down_lt<8>(l, f, c, tau, lS, bl, dl, out, pl);
   }
   template <int LT>
   void mg_up_lt(int l, const LevelDims& f, const LevelDims& c, c128 tau, int lS, const cx<R>* bl, const cx<R>* dl,
                 const cx<R>* xcoarse, cx<R>* out) {
     const int lNC = lS - ilog2(LT);
-    if (LT * sizeof(cx<R>) <= 32 && rows_for(f, lNC)) {
+    if (lanes_rows(f, lS, LT)) {
       leg_rows<true, LT>(l, f, c, tau, lS, lNC, bl, dl, xcoarse, out);
       return;
     }
@@ -1547,15 +1566,15 @@ template <typename R, typename Op, typename OpD> struct Group {
       k_mg_up_chain2d<Op, R, 16><<<g, BS, 0, st>>>(c, tau, mg_omega, B.all_done);
     }
   }
-  void tail2d(int t, unsigned gt, c128 tau, int lS, const cx<R>* bl, cx<R>* xt) {
+  void tail2d(int t, unsigned gt, c128 tau, int lS, const cx<R>* bl, cx<R>* xt, bool pl) {
     if constexpr (Op::NB == 4) {
       const LevelDims d = mg_dims(t);
       const bool top4 = tail2d_top4(t);
       const int J = mg_levels() - t - (top4 ? 1 : 0);
       const size_t lds = (size_t)t2_lds_elems(top4) * sizeof(cx<R>);
       auto go = [&](auto kern) {
-        kern<<<gt, MG_TAIL_THREADS, lds, st>>>(d.nx, d.ny, J, lS > 0 && t < lds_tail_level(lS) ? 1 : 0, tau, mg_omega,
-                                               lS, (const R*)B.mpack, bl, xt, vsc, B.all_done);
+        kern<<<gt, MG_TAIL_THREADS, lds, st>>>(d.nx, d.ny, J, lS > 0 && t < lds_tail_level(lS) ? 1 : 0, pl ? 1 : 0,
+                                               tau, mg_omega, lS, (const R*)B.mpack, bl, xt, vsc, B.all_done);
       };
       if constexpr (c64) {
         if (top4) {
@@ -1572,6 +1591,7 @@ template <typename R, typename Op, typename OpD> struct Group {
       const int S_ = 1 << lS;
       const int t = mg_tail_level(lS);
       const int gdown = std::min(t, Lv - 1);   // levels whose down leg runs on the grid
+      const bool pl = tail_planar(t, lS, from);
       const cx<R>* bl = from > 0 ? B.mb[from - 1] : b0;
       // the last legs above the tail as one chain
       const int dchain = chain_ok(lS) && gdown - from >= 2 ? std::min(MGC_F, gdown - from) : 0;
@@ -1581,7 +1601,7 @@ template <typename R, typename Op, typename OpD> struct Group {
         if (tile3_for(f)) {
           leg_tile3<false>(l, f, c, tau, lS, bl, dl, nullptr, B.mb[l]);
         } else if (lS > 0 && lane_chunks()) {
-          mg_down_lanes(l, f, c, tau, lS, bl, dl, B.mb[l]);
+          mg_down_lanes(l, f, c, tau, lS, bl, dl, B.mb[l], pl && l + 1 == t);
         } else {
           const dim3 g((unsigned)((((long)c.nx * S_ << (Op::NB / 2)) + BS - 1) / BS), (unsigned)c.ny, (unsigned)c.nz);
           k_mg_down<Op, R><<<g, BS, 0, st>>>(mg_op<Op, R>(op, l), f, c, tau, mg_omega, lS, bl, dl, B.mb[l],
@@ -1597,7 +1617,7 @@ template <typename R, typename Op, typename OpD> struct Group {
         cx<R>* xt = t == 0 ? uout : B.mx[t - 1];   // mg_ta, mg_lds: laid out by mg_prepare
         const int lg = tail_lg(lS);
         const unsigned gt = 1u << (lS - lg);
-        if (tail2d_level(lS) == t) tail2d(t, gt, tau, lS, bl, xt);
+        if (tail2d_level(lS) == t) tail2d(t, gt, tau, lS, bl, xt, pl);
         else if (mg_lds > MG_TAIL_LDS)
           k_mg_tail<Op, R, MG_TAIL_LDS_MAX><<<gt, MG_TAIL_THREADS, (size_t)mg_lds, st>>>(
               mg_ta, tau, mg_omega, lg, lS, B.mpack, bl, xt, vsc, B.all_done);
