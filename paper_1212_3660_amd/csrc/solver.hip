@@ -2244,12 +2244,18 @@ template <typename OpD>
 static int residual_rows(const OpD& opd, long n, int S, int s_real, int nf, const c128* sigma, const c128* bint,
                          const c128* X, const c128* rs, int mode, c128* rpart, c128* rrow, hipStream_t st) {
   int Gr = resid_grid(n);
-  if constexpr (OpD::NB > 0) {
-    constexpr int JR = 4;
-    Gr = std::min(Gr, resid_fv_tiles(opd));   // no block without a tile
-    const dim3 gf(Gr, (nf + JR - 1) / JR, s_real);
-    if (mode == 0) k_resid_fv<OpD, JR, 0><<<gf, BS, 0, st>>>(opd, S, nf, sigma, bint, X, rs, rpart);
-    else k_resid_fv<OpD, JR, 1><<<gf, BS, 0, st>>>(opd, S, nf, sigma, bint, X, rs, rpart);
+  // A grid's march is a chain of round trips over few waves: below 3 Mi entries
+  // of X a thread to a cell is no slower (24^3, 50 shifts: 76 us a call against 62;
+  // 64^3, 10 shifts: 80 against 79; 640^2, 20 shifts: 83 against 103).
+  const bool march = OpD::NB > 0 && (long)n * nf * s_real >= (3L << 20);
+  if (march) {
+    if constexpr (OpD::NB > 0) {
+      constexpr int JR = 4;
+      Gr = std::min(Gr, resid_fv_tiles(opd));   // no block without a tile
+      const dim3 gf(Gr, (nf + JR - 1) / JR, s_real);
+      if (mode == 0) k_resid_fv<OpD, JR, 0><<<gf, BS, 0, st>>>(opd, S, nf, sigma, bint, X, rs, rpart);
+      else k_resid_fv<OpD, JR, 1><<<gf, BS, 0, st>>>(opd, S, nf, sigma, bint, X, rs, rpart);
+    }
   } else if (S >= 4) {
     constexpr int JR = 8;
     k_resid_jr<OpD, JR><<<dim3(Gr, (nf + JR - 1) / JR, s_real), BS, 0, st>>>(opd, n, S, nf, sigma, bint, X, rs, mode,
