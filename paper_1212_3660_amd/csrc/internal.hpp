@@ -79,6 +79,9 @@ struct shk_problem {
 
 namespace shk {
 
+// hipMalloc; where it fails, once more after the step calls' kept scratch is freed.
+hipError_t device_malloc(void** ptr, size_t bytes);
+
 int solve_all(shk_problem* p, const shk_params* prm, int n_shifts, const c128* sigma, int n_rhs,
               const c128* b, c128* x, shk_status* st, void* ws, size_t ws_bytes,
               hipStream_t stream, int ptr_kind);

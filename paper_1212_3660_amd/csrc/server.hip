@@ -240,7 +240,7 @@ int shk_server_create(size_t mem_budget_bytes, int max_slots, void* device_arena
     s->arena = static_cast<char*>(device_arena);
   } else {
     void* a = nullptr;
-    if (hipMalloc(&a, s->budget) != hipSuccess) {
+    if (shk::device_malloc(&a, s->budget) != hipSuccess) {
       delete s;
       return shk::fail(SHK_ERR_OOM, "server arena allocation");
     }

@@ -76,7 +76,7 @@ static thread_local Pinned g_pinned;
 // SCRATCH_BLOCKS blocks of SCRATCH_BYTES in all, larger ones are not kept.  A
 // block comes back only from a call that has waited for its stream (idle), so
 // any thread and stream may take it; the blocks are freed when the last problem
-// is destroyed and when the device runs out of memory.
+// is destroyed and when a device allocation of the library fails (giving_way).
 constexpr int SCRATCH_BLOCKS = 8;
 constexpr size_t SCRATCH_BYTES = size_t(256) << 20;
 struct ScratchPool {
@@ -93,6 +93,10 @@ struct ScratchPool {
   void trim() {
     std::lock_guard<std::mutex> g(mu);
     while (!blocks.empty()) drop(0);
+  }
+  bool keeps() {
+    std::lock_guard<std::mutex> g(mu);
+    return !blocks.empty();
   }
   hipError_t take(size_t bytes, void** p, size_t* got, int* dev) {
     hipError_t e = hipGetDevice(dev);
@@ -113,11 +117,7 @@ struct ScratchPool {
       }
     }
     *got = bytes;
-    e = hipMalloc(p, bytes);
-    if (e == hipSuccess) return e;
-    (void)hipGetLastError();
-    trim();
-    return hipMalloc(p, bytes);
+    return device_malloc(p, bytes);
   }
   void put(void* p, size_t bytes, int dev) {
     std::lock_guard<std::mutex> g(mu);
@@ -146,6 +146,23 @@ static ScratchPool& scratch_pool() {
   static ScratchPool* pool = new ScratchPool;   // never destroyed: the runtime may be gone by then
   return *pool;
 }
+
+// Device allocation alloc(); if it fails while blocks are kept, these are freed
+// and it is tried again.  A failure is returned, not left as the last error.
+template <typename A> static hipError_t giving_way(A&& alloc) {
+  hipError_t e = alloc();
+  if (e == hipSuccess) return e;
+  (void)hipGetLastError();
+  if (!scratch_pool().keeps()) return e;
+  scratch_pool().trim();
+  e = alloc();
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e;
+}
+hipError_t device_malloc(void** ptr, size_t bytes) {
+  return giving_way([&] { return hipMalloc(ptr, bytes); });
+}
+
 struct DevBuf {
   void* p = nullptr;
   size_t bytes = 0;
@@ -259,7 +276,7 @@ static hipError_t dev_alloc(shk_problem* p, void** ptr, size_t bytes, hipStream_
     *ptr = p->bump->take(bytes);
     return *ptr ? hipSuccess : hipErrorOutOfMemory;
   }
-  return hipMallocAsync(ptr, bytes, st);
+  return giving_way([&] { return hipMallocAsync(ptr, bytes, st); });
 }
 
 void problem_free(shk_problem* p, hipStream_t st) {
@@ -422,14 +439,14 @@ int problem_setup_csr(shk_problem* p, const int* rowptr, const int* col, const d
   SHK_HIP(hipGetDevice(&p->device));
   p->nnz = nnz;
   p->nx = (int)std::ceil(std::sqrt((double)n));
-  SHK_HIP(hipMallocAsync((void**)&p->rowptr, (n + 1) * sizeof(int), st));
-  SHK_HIP(hipMallocAsync((void**)&p->col, std::max<long>(nnz, 1) * sizeof(int), st));
-  SHK_HIP(hipMallocAsync((void**)&p->val, std::max<long>(nnz, 1) * sizeof(double), st));
-  SHK_HIP(hipMallocAsync((void**)&p->val32, std::max<long>(nnz, 1) * sizeof(float), st));
-  SHK_HIP(hipMallocAsync((void**)&p->diag, n * sizeof(double), st));
-  SHK_HIP(hipMallocAsync((void**)&p->mdiag, n * sizeof(double), st));
-  SHK_HIP(hipMallocAsync((void**)&p->dK, n * sizeof(double), st));
-  SHK_HIP(hipMallocAsync((void**)&p->dK32, n * sizeof(float), st));
+  SHK_HIP(dev_alloc(p, (void**)&p->rowptr, (n + 1) * sizeof(int), st));
+  SHK_HIP(dev_alloc(p, (void**)&p->col, std::max<long>(nnz, 1) * sizeof(int), st));
+  SHK_HIP(dev_alloc(p, (void**)&p->val, std::max<long>(nnz, 1) * sizeof(double), st));
+  SHK_HIP(dev_alloc(p, (void**)&p->val32, std::max<long>(nnz, 1) * sizeof(float), st));
+  SHK_HIP(dev_alloc(p, (void**)&p->diag, n * sizeof(double), st));
+  SHK_HIP(dev_alloc(p, (void**)&p->mdiag, n * sizeof(double), st));
+  SHK_HIP(dev_alloc(p, (void**)&p->dK, n * sizeof(double), st));
+  SHK_HIP(dev_alloc(p, (void**)&p->dK32, n * sizeof(float), st));
   SHK_HIP(hipMemcpyAsync(p->rowptr, rowptr, (n + 1) * sizeof(int), hipMemcpyHostToDevice, st));
   SHK_HIP(hipMemcpyAsync(p->col, col, nnz * sizeof(int), hipMemcpyHostToDevice, st));
   SHK_HIP(hipMemcpyAsync(p->val, val, nnz * sizeof(double), hipMemcpyHostToDevice, st));
@@ -2516,7 +2533,7 @@ int solve_all(shk_problem* p, const shk_params* prm, int nf, const c128* sigma, 
   const size_t need = workspace_bytes(p, prm, nf, n_rhs, host_x);
   void* own = nullptr;
   if (!ws) {
-    if (hipMalloc(&own, need) != hipSuccess) return fail(SHK_ERR_OOM, "workspace allocation failed");
+    if (device_malloc(&own, need) != hipSuccess) return fail(SHK_ERR_OOM, "workspace allocation failed");
     ws = own;
   } else if (ws_bytes < need) {
     return fail(SHK_ERR_WORKSPACE, "workspace too small: need " + std::to_string(need) + " bytes");
