@@ -71,7 +71,7 @@ struct shk_problem {
   float* dK32 = nullptr;
   double* mdiag = nullptr;          // per-row mass (CSR only)
   long long nnz = 0;
-  bool counted = false;             // set up: the step calls' scratch lives as long as some problem does
+  bool counted = false;             // set up: the step calls' scratch is kept as long as some problem lives
   std::vector<shk::MgLevel> mg;     // coarse levels (finite-volume problems)
   shk::Bump* bump = nullptr;        // device arrays from this region instead of the HIP allocator
   int max_dim() const { return nx > ny ? (nx > nz ? nx : nz) : (ny > nz ? ny : nz); }

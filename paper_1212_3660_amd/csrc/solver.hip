@@ -73,10 +73,12 @@ static thread_local Pinned g_pinned;
 
 // Device scratch of the step-level calls.  An allocation and its release cost
 // those calls 50 to 300 us, so blocks are kept for the next call: at most
-// SCRATCH_BLOCKS blocks of SCRATCH_BYTES in all, larger ones are not kept.  A
-// block comes back only from a call that has waited for its stream (idle), so
-// any thread and stream may take it; the blocks are freed when the last problem
-// is destroyed and when a device allocation of the library fails (giving_way).
+// SCRATCH_BLOCKS blocks of SCRATCH_BYTES in all, larger ones are not kept, and
+// only while a problem with device arrays of its own exists (some step calls take
+// none, and nothing else would tell when they are done).  A block comes back only
+// from a call that has waited for its stream (idle), so any thread and stream may
+// take it; the blocks are freed when the last problem is destroyed and when a
+// device allocation of the library fails (giving_way).
 constexpr int SCRATCH_BLOCKS = 8;
 constexpr size_t SCRATCH_BYTES = size_t(256) << 20;
 struct ScratchPool {
@@ -121,7 +123,7 @@ struct ScratchPool {
   }
   void put(void* p, size_t bytes, int dev) {
     std::lock_guard<std::mutex> g(mu);
-    if (bytes > SCRATCH_BYTES) {
+    if (problems == 0 || bytes > SCRATCH_BYTES) {
       (void)hipFree(p);
       return;
     }
@@ -134,12 +136,9 @@ struct ScratchPool {
     ++problems;
   }
   void problem_down() {
-    bool last;
-    {
-      std::lock_guard<std::mutex> g(mu);
-      last = --problems == 0;
-    }
-    if (last) trim();
+    std::lock_guard<std::mutex> g(mu);
+    if (--problems > 0) return;
+    while (!blocks.empty()) drop(0);
   }
 };
 static ScratchPool& scratch_pool() {
@@ -279,6 +278,14 @@ static hipError_t dev_alloc(shk_problem* p, void** ptr, size_t bytes, hipStream_
   return giving_way([&] { return hipMallocAsync(ptr, bytes, st); });
 }
 
+// A problem of the server lives in its request's region and counts for nothing:
+// the end of a request frees no device memory, which would wait for the others'.
+static void problem_counted(shk_problem* p) {
+  if (p->bump) return;
+  p->counted = true;
+  scratch_pool().problem_up();
+}
+
 void problem_free(shk_problem* p, hipStream_t st) {
   if (p->counted) {
     p->counted = false;
@@ -413,8 +420,7 @@ int problem_setup_fv(shk_problem* p, const double* K, double Ss, double h, hipSt
   p->cellK = Kd;   // kept for sensitivities
   SHK_TRY(mg_setup(p, st));
   SHK_HIP(hipStreamSynchronize(st));
-  p->counted = true;
-  scratch_pool().problem_up();
+  problem_counted(p);
   return SHK_OK;
 }
 
@@ -457,8 +463,7 @@ int problem_setup_csr(shk_problem* p, const int* rowptr, const int* col, const d
   SHK_HIP(hipMemcpyAsync(p->dK, dg.data(), n * sizeof(double), hipMemcpyHostToDevice, st));
   SHK_HIP(hipMemcpyAsync(p->dK32, dg32.data(), n * sizeof(float), hipMemcpyHostToDevice, st));
   SHK_HIP(hipStreamSynchronize(st));
-  p->counted = true;
-  scratch_pool().problem_up();
+  problem_counted(p);
   return SHK_OK;
 }
 

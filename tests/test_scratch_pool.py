@@ -108,3 +108,17 @@ def test_kept_blocks_give_way(fake, what):
         fake.fake_limit(NONE)
         assert least_squares(10) == 0
     """ % what)
+
+
+def test_nothing_is_kept_without_a_problem(fake):
+    _run(fake, """
+        assert least_squares(1000) == 0
+        assert fake.fake_live() == 0, fake.fake_live()
+        rc, p = problem()
+        used = fake.fake_live()
+        assert least_squares(1000) == 0 and fake.fake_live() > used
+        destroy(p)
+        assert fake.fake_live() == 0, fake.fake_live()
+        assert least_squares(1000) == 0
+        assert fake.fake_live() == 0, fake.fake_live()
+    """)
