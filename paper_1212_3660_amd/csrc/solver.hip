@@ -83,38 +83,40 @@ constexpr int SCRATCH_BLOCKS = 8;
 constexpr size_t SCRATCH_BYTES = size_t(256) << 20;
 struct ScratchPool {
   struct Block { void* p; size_t bytes; int dev; };
+  // nothing here allocates, so nothing throws out of a destructor or a C entry point
   std::mutex mu;
-  std::vector<Block> blocks;   // oldest first
+  Block blocks[SCRATCH_BLOCKS];   // oldest first
+  int count = 0;
   size_t held = 0;
   int problems = 0;
-  void drop(size_t i) {
-    (void)hipFree(blocks[i].p);
-    held -= blocks[i].bytes;
-    blocks.erase(blocks.begin() + (long)i);
+  Block remove(int i) {
+    const Block b = blocks[i];
+    held -= b.bytes;
+    std::copy(blocks + i + 1, blocks + count, blocks + i);
+    --count;
+    return b;
   }
-  void trim() {
+  void drop_oldest() { (void)hipFree(remove(0).p); }
+  bool trim() {   // false: there was nothing to free
     std::lock_guard<std::mutex> g(mu);
-    while (!blocks.empty()) drop(0);
-  }
-  bool keeps() {
-    std::lock_guard<std::mutex> g(mu);
-    return !blocks.empty();
+    const bool any = count > 0;
+    while (count > 0) drop_oldest();
+    return any;
   }
   hipError_t take(size_t bytes, void** p, size_t* got, int* dev) {
-    hipError_t e = hipGetDevice(dev);
+    const hipError_t e = hipGetDevice(dev);
     if (e != hipSuccess) return e;
     {
       std::lock_guard<std::mutex> g(mu);
-      size_t best = blocks.size();
-      for (size_t i = 0; i < blocks.size(); ++i)
+      int best = -1;
+      for (int i = 0; i < count; ++i)
         if (blocks[i].dev == *dev && blocks[i].bytes >= bytes && blocks[i].bytes <= 4 * bytes + (size_t(1) << 20) &&
-            (best == blocks.size() || blocks[i].bytes < blocks[best].bytes))
+            (best < 0 || blocks[i].bytes < blocks[best].bytes))
           best = i;
-      if (best < blocks.size()) {
-        *p = blocks[best].p;
-        *got = blocks[best].bytes;
-        held -= blocks[best].bytes;
-        blocks.erase(blocks.begin() + (long)best);
+      if (best >= 0) {
+        const Block b = remove(best);
+        *p = b.p;
+        *got = b.bytes;
         return hipSuccess;
       }
     }
@@ -127,8 +129,8 @@ struct ScratchPool {
       (void)hipFree(p);
       return;
     }
-    while (!blocks.empty() && ((int)blocks.size() >= SCRATCH_BLOCKS || held + bytes > SCRATCH_BYTES)) drop(0);
-    blocks.push_back({p, bytes, dev});
+    while (count > 0 && (count >= SCRATCH_BLOCKS || held + bytes > SCRATCH_BYTES)) drop_oldest();
+    blocks[count++] = {p, bytes, dev};
     held += bytes;
   }
   void problem_up() {
@@ -138,7 +140,7 @@ struct ScratchPool {
   void problem_down() {
     std::lock_guard<std::mutex> g(mu);
     if (--problems > 0) return;
-    while (!blocks.empty()) drop(0);
+    while (count > 0) drop_oldest();
   }
 };
 static ScratchPool& scratch_pool() {
@@ -152,8 +154,7 @@ template <typename A> static hipError_t giving_way(A&& alloc) {
   hipError_t e = alloc();
   if (e == hipSuccess) return e;
   (void)hipGetLastError();
-  if (!scratch_pool().keeps()) return e;
-  scratch_pool().trim();
+  if (!scratch_pool().trim()) return e;
   e = alloc();
   if (e != hipSuccess) (void)hipGetLastError();
   return e;

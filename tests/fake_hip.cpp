@@ -6,13 +6,12 @@
 #include <cstddef>
 #include <cstdlib>
 #include <cstring>
-#include <map>
 #include <mutex>
 #include <new>
 
 namespace {
 std::mutex mu;
-std::map<void*, size_t> blocks;
+constexpr size_t HEAD = 64;   // a block's size stands before it
 size_t live = 0, limit = ~size_t(0);
 int last = 0;
 constexpr int OOM = 2;
@@ -23,8 +22,9 @@ int gate = 0;
 int alloc(void** p, size_t bytes) {
   std::lock_guard<std::mutex> g(mu);
   if (bytes > limit - (live < limit ? live : limit)) return last = OOM;
-  *p = std::calloc(bytes ? bytes : 1, 1);
-  blocks[*p] = bytes;
+  char* q = static_cast<char*>(std::calloc(bytes + HEAD, 1));
+  std::memcpy(q, &bytes, sizeof bytes);
+  *p = q + HEAD;
   live += bytes;
   return 0;
 }
@@ -37,18 +37,29 @@ int release(void* p) {
     cv.wait_for(g, std::chrono::seconds(10), [] { return gate == 0; });
     gate = 0;
   }
-  auto it = blocks.find(p);
-  if (it == blocks.end()) return last = 1;
-  live -= it->second;
-  blocks.erase(it);
-  std::free(p);
+  char* q = static_cast<char*>(p) - HEAD;
+  size_t bytes;
+  std::memcpy(&bytes, q, sizeof bytes);
+  live -= bytes;
+  std::free(q);
   return 0;
 }
+int no_new = 0;
 }  // namespace
+
+// the library's host allocations
+void* operator new(size_t n) {
+  if (no_new) throw std::bad_alloc();
+  if (void* p = std::malloc(n ? n : 1)) return p;
+  throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
 
 extern "C" {
 size_t fake_live() { std::lock_guard<std::mutex> g(mu); return live; }
 void fake_limit(size_t bytes) { std::lock_guard<std::mutex> g(mu); limit = bytes; }
+void fake_no_new(int on) { no_new = on; }   // from now on they fail
 void fake_gate_arm() { std::lock_guard<std::mutex> g(mu); gate = 1; }
 int fake_gate_entered() {   // waits until a hipFree stands at the gate
   std::unique_lock<std::mutex> g(mu);

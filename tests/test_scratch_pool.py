@@ -38,6 +38,10 @@ def least_squares(nf, k=20):
     a = [np.zeros(s, complex) for s in ((k + 1) * k, k, nf, nf * k)]
     return L.shk_shifted_lsq(k, ptr(a[0]), ptr(a[1]), nf, ptr(a[2]), C.c_double(1.0), ptr(a[3]),
                              ptr(np.zeros(nf * k)), 0)
+
+def orthogonalize(n, k=2):
+    V, w, h = np.zeros((k + 1, n), complex), np.zeros(n, complex), np.zeros(k + 1, complex)
+    return L.shk_orthogonalize(C.c_longlong(n), 1, k, ptr(V), ptr(w), ptr(h), 0, 0, None)
 """
 
 
@@ -121,4 +125,15 @@ def test_nothing_is_kept_without_a_problem(fake):
         assert fake.fake_live() == 0, fake.fake_live()
         assert least_squares(1000) == 0
         assert fake.fake_live() == 0, fake.fake_live()
+    """)
+
+
+def test_giving_a_block_back_needs_no_host_memory(fake):
+    """It happens in a destructor, where an exception ends the process."""
+    _run(fake, """
+        rc, p = problem()
+        fake.fake_no_new(1)
+        rc = orthogonalize(500)
+        fake.fake_no_new(0)
+        assert rc == 0
     """)
