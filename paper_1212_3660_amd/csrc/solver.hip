@@ -83,7 +83,16 @@ constexpr int SCRATCH_BLOCKS = 8;
 constexpr size_t SCRATCH_BYTES = size_t(256) << 20;
 struct ScratchPool {
   struct Block { void* p; size_t bytes; int dev; };
-  // nothing here allocates, so nothing throws out of a destructor or a C entry point
+  // Blocks taken out under the lock and freed after it: hipFree waits for the
+  // device, and no other thread's call should wait for that.  Nothing here
+  // allocates, so nothing throws out of a destructor or a C entry point.
+  struct Drop {
+    void* p[SCRATCH_BLOCKS + 1];
+    int n = 0;
+    ~Drop() {
+      for (int i = 0; i < n; ++i) (void)hipFree(p[i]);
+    }
+  };
   std::mutex mu;
   Block blocks[SCRATCH_BLOCKS];   // oldest first
   int count = 0;
@@ -96,12 +105,12 @@ struct ScratchPool {
     --count;
     return b;
   }
-  void drop_oldest() { (void)hipFree(remove(0).p); }
+  void drop_oldest(Drop& d) { d.p[d.n++] = remove(0).p; }
   bool trim() {   // false: there was nothing to free
+    Drop d;
     std::lock_guard<std::mutex> g(mu);
-    const bool any = count > 0;
-    while (count > 0) drop_oldest();
-    return any;
+    while (count > 0) drop_oldest(d);
+    return d.n > 0;
   }
   hipError_t take(size_t bytes, void** p, size_t* got, int* dev) {
     const hipError_t e = hipGetDevice(dev);
@@ -124,12 +133,13 @@ struct ScratchPool {
     return device_malloc(p, bytes);
   }
   void put(void* p, size_t bytes, int dev) {
+    Drop d;
     std::lock_guard<std::mutex> g(mu);
     if (problems == 0 || bytes > SCRATCH_BYTES) {
-      (void)hipFree(p);
+      d.p[d.n++] = p;
       return;
     }
-    while (count > 0 && (count >= SCRATCH_BLOCKS || held + bytes > SCRATCH_BYTES)) drop_oldest();
+    while (count > 0 && (count >= SCRATCH_BLOCKS || held + bytes > SCRATCH_BYTES)) drop_oldest(d);
     blocks[count++] = {p, bytes, dev};
     held += bytes;
   }
@@ -138,9 +148,10 @@ struct ScratchPool {
     ++problems;
   }
   void problem_down() {
+    Drop d;
     std::lock_guard<std::mutex> g(mu);
     if (--problems > 0) return;
-    while (count > 0) drop_oldest();
+    while (count > 0) drop_oldest(d);
   }
 };
 static ScratchPool& scratch_pool() {

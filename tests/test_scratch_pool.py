@@ -128,6 +128,24 @@ def test_nothing_is_kept_without_a_problem(fake):
     """)
 
 
+def test_a_release_holds_up_no_other_call(fake):
+    """hipFree waits for the work on the device: while one thread stands in it
+    with the blocks of the last problem, another thread's call goes through."""
+    _run(fake, """
+        import threading
+        rc, p = problem()
+        assert least_squares(1000) == 0
+        fake.fake_gate_arm()       # taken by the first hipFree: a kept block's
+        t = threading.Thread(target=destroy, args=(p,))
+        t.start()
+        assert fake.fake_gate_entered()
+        assert least_squares(300) == 0
+        assert fake.fake_gate_open() == 1
+        t.join()
+        assert fake.fake_live() == 0
+    """)
+
+
 def test_giving_a_block_back_needs_no_host_memory(fake):
     """It happens in a destructor, where an exception ends the process."""
     _run(fake, """
