@@ -1786,6 +1786,12 @@ template <typename Op> static int resid_fv_tiles(const Op& op) {
   const ResidTiles<Op> t(op);
   return (int)std::min<long>((long)t.x * t.y * t.z, 1L << 30);
 }
+// Part of the tiles' columns and planes that carry cells.
+template <typename Op> static double resid_fv_share(const Op& op) {
+  const ResidTiles<Op> t(op);
+  if constexpr (Op::NB == 6) return (double)op.nx / (t.x * WAVE) * op.nz / (t.z * NWAVE);
+  else return (double)op.nx / (t.x * (double)(NWAVE * WAVE));
+}
 template <typename Op, int JR, int MODE>
 __global__ void __launch_bounds__(BS) k_resid_fv(Op op, int S, int nf, const c128* __restrict__ sigma,
                                                  const c128* __restrict__ bint, const c128* __restrict__ X,

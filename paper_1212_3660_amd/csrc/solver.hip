@@ -2289,10 +2289,29 @@ template <typename OpD>
 static int residual_rows(const OpD& opd, long n, int S, int s_real, int nf, const c128* sigma, const c128* bint,
                          const c128* X, const c128* rs, int mode, c128* rpart, c128* rrow, hipStream_t st) {
   int Gr = resid_grid(n);
-  // A grid's march is a chain of round trips over few waves: below 3 Mi entries
-  // of X a thread to a cell is no slower (24^3, 50 shifts: 76 us a call against 62;
-  // 64^3, 10 shifts: 80 against 79; 640^2, 20 shifts: 83 against 103).
-  const bool march = OpD::NB > 0 && (long)n * nf * s_real >= (3L << 20);
+  // A grid's rows are marched where that is faster than a thread to a cell.  A
+  // march pays for whole tiles (256 cells of a row in 2-D, 64 of four planes in
+  // 3-D) and whole groups of shifts: on a thin grid, or with few shifts, most of it
+  // is padding (one lane, kernels alone, marched and not: 1048576 x 1 cells, 8
+  // shifts: 3.3 ms, 0.04; 10485 x 100, 8 shifts: 62 us, 47; 13981 x 300, 3 shifts:
+  // 146, 129; 64 x 128 x 16, 100 shifts, a quarter in use: 152, 102).  And it is a
+  // chain of round trips over few waves, which wants 4 Mi entries of X (512^2, 20
+  // shifts, 5 Mi: 28, 35; 3495 x 300, 3 Mi: 39, 31), in 3-D, where a tile is read
+  // with the planes beside it, 16 Mi unless several lanes share its b (64^3, 50
+  // shifts, 12.5 Mi: 113, 98; 100 shifts: 184, 241).  In 2-D below 8 Mi or 16
+  // shifts the gain at full use is 1.2 to 1.5, so 0.6 of the lanes and shifts have
+  // to be in use; elsewhere it is 1.5 to 2, and 0.38 are enough (10485 x 100, 20
+  // shifts, 0.39: 136, 162).
+  bool march = false;
+  if constexpr (OpD::NB > 0) {
+    constexpr bool D3 = OpD::NB == 6;
+    const bool lanes = S >= 4;
+    const long items = n * nf * s_real;
+    const int JR = lanes ? 8 : 4;
+    const double used = resid_fv_share(opd) * nf / (JR * (double)((nf + JR - 1) / JR));
+    march = items >= (D3 && !lanes ? 16L << 20 : 4L << 20) &&
+            used >= (!D3 && !lanes && (nf < 16 || items < (8L << 20)) ? 0.6 : 0.38);
+  }
   if (march) {
     // With several lanes a line of b holds the cell's other lanes and comes once
     // for each block of shifts: eight of them (128^3, 8 lanes, 16 shifts: 2.94 -> 2.24 ms).
