@@ -21,7 +21,10 @@
 // The next adjoint solution's loads are in flight while this one's entries are
 // formed, and dT / d ln K_c is folded into the forward differences once (256 x 256,
 // 50 shifts, 8 x 8, complex64: 910 -> 810 us; two ahead, or tiles of 2 or 8
-// forward solutions, 850 to 1030 us; the stores alone take 330 us).
+// forward solutions, 850 to 1030 us; the stores alone take 330 us).  In 3-D the
+// loads ahead have to fit three wavefronts a SIMD: with two, calls of few receivers
+// lost to the form without them (64^3, 12 shifts, complex64, 8 x 1: 499 us without,
+// 572 with two wavefronts, 468 with three; 8 x 8: 1295, 1163, 1015).
 #pragma once
 #include "kernels.hpp"
 
@@ -43,7 +46,7 @@ struct SensArgs {
 // xcd_tile, so one XCD's L2 serves the neighbour rows and the adjoint
 // solutions to every tile of a band of cells.
 template <typename RO, int TS, int NF>
-__global__ void __launch_bounds__(BS) k_sensitivity(SensArgs a, cx<RO>* __restrict__ J) {
+__global__ void __launch_bounds__(BS, NF == 6 ? 3 : 4) k_sensitivity(SensArgs a, cx<RO>* __restrict__ J) {
   const long n = (long)a.nx * a.ny * a.nz;
   const int ntile = (a.ns + TS - 1) / TS;
   const int T = xcd_tile(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
@@ -91,11 +94,16 @@ __global__ void __launch_bounds__(BS) k_sensitivity(SensArgs a, cx<RO>* __restri
     }
   }
   c128 qc, qn[NF];   // the adjoint solution at the cell and its neighbours
+  // the neighbours' indices are formed anew each time: held, they take registers
+  // that three wavefronts a SIMD (3-D: 168 each) do not leave
+  const int step[6] = {-1, 1, -a.nx, a.nx, -pl, pl};
   auto load = [&](int r) {
     const c128* ps = a.psi + n * ((long)j + (long)a.nf * r);
-    qc = ps[c];
+    int cell = (int)c;
+    asm volatile("" : "+v"(cell));
+    qc = ps[cell];
 #pragma unroll
-    for (int q = 0; q < NF; ++q) qn[q] = ps[nb[q]];
+    for (int q = 0; q < NF; ++q) qn[q] = ps[in[q] ? cell + step[q] : cell];
   };
   load(0);
   for (int r = 0; r < a.nr; ++r) {
