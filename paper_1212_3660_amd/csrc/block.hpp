@@ -74,7 +74,8 @@ __global__ void __launch_bounds__(256, 4) k_assemble_mfma(long n, int S, int s_r
   const int r = rem >> 3;
   const long cell0 = ((grp * 8 + (rem & 7)) * 4 + (threadIdx.x >> 6)) * 16;
   if (r >= s_real || cell0 - 16 * (int)(threadIdx.x >> 6) >= n) return;   // whole blocks
-  const int j0 = (int)blockIdx.y * 16 * TN;
+  const int j0 = (int)(blockIdx.y + gridDim.y * blockIdx.z) * 16 * TN;
+  if (j0 >= nf) return;
   d4m re[TN], im[TN];
 #pragma unroll
   for (int t = 0; t < TN; ++t) {

@@ -866,7 +866,8 @@ static void launch_assemble(long n, int S, int s_real, int nf, int kc, int m, co
     // groups of 8 (one per XCD slot) x S lanes
     const long tiles = (n + 63) / 64;
     const long blocks = (tiles + 7) / 8 * 8 * S;
-    const dim3 grid((unsigned)blocks, (unsigned)((nf + 31) / 32));
+    const int js = (nf + 31) / 32, jy = std::min(js, 1 << 15);   // y holds 65,536 blocks at most
+    const dim3 grid((unsigned)blocks, (unsigned)jy, (unsigned)((js + jy - 1) / jy));
     k_assemble_mfma<R, 2><<<grid, 256, 0, st>>>(n, S, s_real, nf, kc, m, Z, cstride, Yb, ascale, X, acc);
     return;
   }
