@@ -914,8 +914,8 @@ static long dot_ipb(long N) {
 // Column groups of its grid: below 4 Mi items its blocks are 8 waves per CU or
 // fewer, each with a column's loads in flight, and the four waves of a block
 // take a column each (512 x 512, complex64, 24 columns: 21 -> 14 us).  Larger
-// ones stream, and w is read once for all columns.
-static int dot_cols(long N, int kc) { return N >= (4L << 20) ? 1 : (kc + NWAVE - 1) / NWAVE; }
+// ones stream, and w is read once for all columns.  The grid's y holds 65,536 groups.
+static int dot_cols(long N, int kc) { return N >= (4L << 20) ? 1 : std::min((kc + NWAVE - 1) / NWAVE, 1 << 16); }
 static int gs_entries_grid(int entries) { return 64 * (((entries + 7) / 8 + 7) / 8); }
 
 template <typename R>

@@ -21,3 +21,19 @@ def test_assemble_of_many_shifts(nf):
     X = torch.full((nf, n), float("nan"), dtype=torch.complex128, device="cuda")
     P.shk_assemble(n, 1, nf, torch.from_numpy(Z).cuda(), torch.from_numpy(Y).cuda(), X)
     assert np.all(np.abs(X.cpu().numpy() - Y * Z) <= 5e-16 * np.abs(Y * Z))
+
+
+def test_gram_schmidt_against_many_columns():
+    """One entry per column, all but the last column zero: w goes into that one."""
+    torch = require_gpu()
+    import paper_1212_3660_amd as P
+    k = 4 * 65536 + 5
+    announce(f"gram-schmidt k={k}")
+    V = torch.zeros(k + 1, dtype=torch.complex128, device="cuda")
+    V[k - 1] = 1.0
+    w = torch.full((1,), 0.75 - 0.5j, dtype=torch.complex128, device="cuda")
+    h = P.shk_orthogonalize(1, k, V, w)
+    want = np.zeros(k + 1, dtype=np.complex128)
+    want[k - 1] = 0.75 - 0.5j
+    assert np.array_equal(h[0], want)
+    assert complex(V[k].cpu()) == 0 and complex(w[0].cpu()) == 0
