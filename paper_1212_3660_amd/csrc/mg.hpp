@@ -213,24 +213,34 @@ __device__ __forceinline__ cx<R> mg_up_cell(const Op& op, const LevelDims& f, co
 // XCD runs at once then span a few planes of its slab, whose planes before and
 // after are still in its L2 (a band of whole planes is too large for it).
 //
-// BACK: the same blocks, each XCD's from its last to its first.  The four large
+// back: the same blocks, each XCD's from its last to its first.  The four large
 // launches of an iteration on several lanes (step, finest restriction, finest
-// prolongation, product) each stream more than the 256 MB Infinity Cache holds,
-// so one that walks the way its predecessor did finds nothing of it there; the
-// step and the prolongations walk backwards, and each launch starts on what the
-// one before it touched last.
-template <bool BACK = false> __device__ __forceinline__ void xcd_block3(int& bx, int& by, int& bz) {
+// prolongation, product) together move far more than the 256 MB Infinity Cache
+// holds, so one that walks the way its predecessor did finds the least of it
+// there; the step and the prolongation walk backwards.  Counters between the L2s
+// and memory count that cache's hits as well and show no difference; the times do
+// (whole solves in turn on one card, the same buffers, spread 0.2 %, prolongation
+// forwards and backwards): 128^3 x 8 lanes 641.6 and 632.5 ms FP64, 387.0 and 381.9
+// mixed; 64^3 x 32 FP64 269.9 and 262.5.  It is worth nothing while a vector fits
+// the cache several times over, and in 2-D with two FP64 lanes it cost (130 x 1000
+// 37.7 and 38.7, 300^2 24.0 and 24.2): a prolongation walks backwards where a vector
+// of its level takes WALK_BACK bytes or more.
+constexpr size_t WALK_BACK = size_t(96) << 20;
+template <typename R> __device__ __forceinline__ bool walk_back(const LevelDims& f, int lS) {
+  return ((size_t)f.n() << lS) * sizeof(cx<R>) >= WALK_BACK;
+}
+__device__ __forceinline__ void xcd_block3(int& bx, int& by, int& bz, bool back = false) {
   const int gx = gridDim.x, gy = gridDim.y;
   const int w = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
   if (gridDim.z > 1 && (gy & 7) == 0) {
-    const int ry = gy >> 3, n8 = gx * ry * gridDim.z, u = BACK ? n8 - 1 - (w >> 3) : w >> 3;
+    const int ry = gy >> 3, n8 = gx * ry * gridDim.z, u = back ? n8 - 1 - (w >> 3) : w >> 3;
     bx = u % gx;
     const int r = u / gx;
     by = (w & 7) * ry + r % ry;
     bz = r / ry;
     return;
   }
-  const int T = BACK ? xcd_tile_rev(w, gx * gy * gridDim.z) : xcd_tile(w, gx * gy * gridDim.z);
+  const int T = back ? xcd_tile_rev(w, gx * gy * gridDim.z) : xcd_tile(w, gx * gy * gridDim.z);
   const int r = T / gx;
   bx = T - r * gx;
   by = r % gy;
@@ -400,7 +410,7 @@ __global__ void __launch_bounds__(BS) k_mg_up_lanes(Op op, LevelDims f, LevelDim
   constexpr int NB = Op::NB;
   int flag = *all_done;
   int bx, j, k;
-  xcd_block3<true>(bx, j, k);
+  xcd_block3(bx, j, k, walk_back<R>(f, lS));
   const int t = bx * BS + threadIdx.x;
   if (t >= (f.nx << lNC)) return;
   const int lc = t & ((1 << lNC) - 1), i = t >> lNC;
@@ -483,7 +493,7 @@ __global__ void __launch_bounds__(BS) k_mg_leg_rows(Op op, LevelDims f, LevelDim
   const int flag = *all_done;
   const int NC = 1 << lNC, S = 1 << lS, SW = BS >> lNC;
   const int nseg = (f.nx + SW - 1) / SW;
-  const int tile = UP ? xcd_tile_rev(blockIdx.x, gridDim.x) : xcd_tile(blockIdx.x, gridDim.x);
+  const int tile = UP && walk_back<R>(f, lS) ? xcd_tile_rev(blockIdx.x, gridDim.x) : xcd_tile(blockIdx.x, gridDim.x);
   const int seg = tile % nseg, rb = tile / nseg;
   const int lc = (int)threadIdx.x & (NC - 1), ci = (int)threadIdx.x >> lNC;
   const int i = seg * SW + ci;
@@ -947,7 +957,7 @@ __global__ void __launch_bounds__(T3T) k_mg_leg_tile3(Op op, LevelDims f, LevelD
   __shared__ cx<R> stg[UP ? 1 : T3Y][UP ? 1 : T3X][LT];   // restriction: the children's sums
   const int flag = *all_done;
   int bxc, by, bz;
-  xcd_block3<UP>(bxc, by, bz);
+  xcd_block3(bxc, by, bz, UP && walk_back<R>(f, lS));
   const int ch = bxc % C, bx = bxc / C;
   if (!chunk_live<LT>(sc, ch * LT)) return;   // the block's chunk has stopped (uniform)
   const int tx = (int)threadIdx.x % T3X, ty = (int)threadIdx.x / T3X;
