@@ -569,13 +569,13 @@ def run(a):
     value = nf * a.steps / (mixed["total_ms"] / 1e3)
     fp64_value = nf * a.steps / (fp64["total_ms"] / 1e3)
     # Roofline unit: one multigrid-COCG inner iteration (the step fused with
-    # the first restriction, the V-cycle's other k_mg_down / k_mg_tail /
+    # the first restriction, the V-cycle's other k_mg_down / k_mg_tail2d /
     # k_mg_up launches, k_cgmg_post), timed
     # with HIP events on the solver's stream around every chunk of iterations
     # inside the timed region; no single launch of it dominates.
     roof = roofline(mixed["prof"], "traffic_mg_iteration_512x512.json",
                     "multigrid-COCG inner iteration, mixed path: k_cgmg_step_down (step fused with the finest "
-                    "restriction), the middle restrictions (k_mg_down_chain2d), k_mg_tail, the middle "
+                    "restriction), the middle restrictions (k_mg_down_chain2d), k_mg_tail2d, the middle "
                     "prolongations (k_mg_up_chain2d), the finest k_mg_up, k_cgmg_post (6 launches; 10 without "
                     "the chains)", "iteration")
     roof_jac = roofline(jac["mixed"]["prof"], "traffic_cg_step_512x512.json",

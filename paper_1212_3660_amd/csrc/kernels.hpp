@@ -638,8 +638,10 @@ __device__ __forceinline__ void cg_compute(const CgCell<Op, R>& L, int t, cx<R> 
 // 8.4 -> 7.8 us a launch, an inner solve of 90 launches 900 -> 767 us with the
 // state's copy kept out of scratch memory).  The registers that hold it leave two
 // wavefronts a SIMD: up to CSR_ROW_WAVES of them, all resident at once, it is
-// the faster form (129,600 rows: 1334 -> 1218 us a solve); above, the loop is
-// (160,000 rows: held 1500, loop 1397 us).
+// the faster form (complex128, 129,600 rows: 1334 -> 1218 us a solve; complex64, 60
+// iterations of 130,682 rows: 923 -> 801); above, the loop is (complex128, 160,000
+// rows: held 1500, loop 1397 us; complex64 as well gains less there, 134,689 rows:
+// 997 -> 954).
 constexpr int CSR_ROW_WAVES = 2048;
 template <typename R> struct CsrRow {
   static constexpr int CE = 6;
@@ -1760,16 +1762,17 @@ __global__ void __launch_bounds__(BS) k_resid_jr(Op op, long n, int S, int nf, c
   }
 }
 
-// The same on a grid operator, JR shifts per block.  The launch reads X once and
-// is bound by that read, so a wave marches RESID_YB rows of 64 cells with the
-// row's x and the rows before and after it in registers for every shift: one
-// load of X per cell and shift, the x neighbours from the lanes beside (the
-// wave's two end lanes load theirs), faces and b once for JR shifts.  In 3-D the
-// four waves of a block march the same rows of four adjacent planes and load the
-// planes before and after, mostly from the CU's L1; in 2-D they take four
-// adjacent row segments.  Tiles (planes, rows, segments, the last fastest) go
-// over the grid in XCD bands.  512 x 512 x 200 shifts: 397 us with a cell's five
-// values loaded at every cell and indices divided, now 176 us.
+// The same on a grid operator, JR shifts per block.  Bound by the read of X: a wave
+// marches RESID_YB rows of 64 cells with the row's x and the rows before and after
+// it in registers for every shift, so in 2-D X comes once (and a row more at either
+// end of a band): one load of X per cell and shift, the x neighbours from the lanes
+// beside (the wave's two end lanes load theirs), faces and b once for JR shifts.  In
+// 3-D the four waves of a block march the same rows of four adjacent planes and load
+// the planes before and after too, three loads a cell and shift of which the caches
+// serve a part only.  In 2-D the waves take four adjacent row segments.  Tiles
+// (planes, rows, segments, the last fastest) go over the grid in XCD bands.  The
+// kernel alone on 512 x 512, 200 shifts: 375 us a thread to a cell (five loads and
+// the indices divided), 177 marched; 128^3, 100 shifts: 2016, 1306.
 constexpr int RESID_YB = 16;
 template <typename Op> struct ResidTiles {   // tiles along x, y and z
   int x, y, z;

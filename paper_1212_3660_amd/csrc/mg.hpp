@@ -151,6 +151,10 @@ template <typename T> __device__ __forceinline__ T* opaque(T* p) {
 // b_c - (A x1)_c after the first sweep x1 = omega D^-1 b (x1 at the stencil
 // neighbours formed on the fly).  gb(c), gd(c): b and D^-1 at fine cell c
 // for the lane.  Callers pass coordinates so that no index is divided.
+// k_mg_tail2d writes out the order in which the compiler contracts this function
+// and mg_up_cell (and their forms in the lane kernels): after a change here, or of
+// the compiler, its complex64 bits differ from the LDS tail's, which a test compares,
+// and its cmul_n / cmul_s choices have to be read off again.
 template <typename Op, typename R, typename GB, typename GD>
 __device__ __forceinline__ cx<R> mg_down_fine(const Op& op, int i, int j, int k, int c, cx<R> tr, R om, GB gb,
                                               GD gd) {
