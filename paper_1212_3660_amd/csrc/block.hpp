@@ -149,31 +149,15 @@ __global__ void __launch_bounds__(64) k_blk_gram(const cx<TIn>* __restrict__ A, 
       re[a][b] = V4{0, 0, 0, 0};
       im[a][b] = V4{0, 0, 0, 0};
     }
-  cx<TIn> av[TM], bv[TN];
-  // the next PF steps' operands: the two waves a SIMD has here do not cover a
-  // load by themselves (256 x 256 x 64 columns, 8 blocks, FP64: 560 us without, 460 with)
-  constexpr int PF = 2;
-  cx<TIn> ap[PF][TM], bp[PF][TN];
-  auto load = [&](long c, int d) {
+  auto load = [&](long c, cx<TIn> (&av)[TM], cx<TIn> (&bv)[TN]) {
     const long cell = c + g;
     const bool ok = cell < c1;
 #pragma unroll
-    for (int a = 0; a < TM; ++a) ap[d][a] = ok ? Ai[cell * S + 16 * a + m] : cx<TIn>{0, 0};
+    for (int a = 0; a < TM; ++a) av[a] = ok ? Ai[cell * S + 16 * a + m] : cx<TIn>{0, 0};
 #pragma unroll
-    for (int b = 0; b < TN; ++b) bp[d][b] = ok ? B[cell * S + 16 * (nb0 + b) + m] : cx<TIn>{0, 0};
+    for (int b = 0; b < TN; ++b) bv[b] = ok ? B[cell * S + 16 * (nb0 + b) + m] : cx<TIn>{0, 0};
   };
-#pragma unroll
-  for (int d = 0; d < PF; ++d) load(c0 + 4 * d, d);
-  for (long cb = c0; cb < c1; cb += 4 * PF)
-#pragma unroll
-  for (int d = 0; d < PF; ++d) {
-    const long c = cb + 4 * d;
-    if (c >= c1) break;
-#pragma unroll
-    for (int a = 0; a < TM; ++a) av[a] = ap[d][a];
-#pragma unroll
-    for (int b = 0; b < TN; ++b) bv[b] = bp[d][b];
-    load(c + 4 * PF, d);
+  auto product = [&](const cx<TIn> (&av)[TM], const cx<TIn> (&bv)[TN]) {
 #pragma unroll
     for (int a = 0; a < TM; ++a) {
       const TAcc ar = (TAcc)av[a].re, ai = (TAcc)av[a].im;
@@ -185,6 +169,34 @@ __global__ void __launch_bounds__(64) k_blk_gram(const cx<TIn>* __restrict__ A, 
         im[a][b] = mfma16(ar, bi, im[a][b]);
         im[a][b] = mfma16(ai, -br, im[a][b]);
       }
+    }
+  };
+  if constexpr (std::is_same<TAcc, double>::value) {
+    // the next PF steps' operands: the two waves a SIMD has here do not cover a
+    // load by themselves (65,536 cells, 64 columns, 12 blocks, FP64: 529 us without, 438 with)
+    constexpr int PF = 2;
+    cx<TIn> av[TM], bv[TN], ap[PF][TM], bp[PF][TN];
+#pragma unroll
+    for (int d = 0; d < PF; ++d) load(c0 + 4 * d, ap[d], bp[d]);
+    for (long cb = c0; cb < c1; cb += 4 * PF)
+#pragma unroll
+      for (int d = 0; d < PF; ++d) {
+        const long c = cb + 4 * d;
+        if (c >= c1) break;
+#pragma unroll
+        for (int a = 0; a < TM; ++a) av[a] = ap[d][a];
+#pragma unroll
+        for (int b = 0; b < TN; ++b) bv[b] = bp[d][b];
+        load(c + 4 * PF, ap[d], bp[d]);
+        product(av, bv);
+      }
+  } else {
+    // sixteen tiles a wave leave no registers for operands ahead (the same blocks
+    // in FP32: 263 us so, 316 with two steps ahead), and fewer tiles gain nothing
+    for (long c = c0; c < c1; c += 4) {
+      cx<TIn> av[TM], bv[TN];
+      load(c, av, bv);
+      product(av, bv);
     }
   }
   cx<TAcc>* out = part + ((size_t)i * nch + chunk) * S * S;
