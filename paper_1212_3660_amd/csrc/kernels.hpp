@@ -26,8 +26,13 @@ constexpr int NWAVE = BS / WAVE;
 // over its 8 XCDs, each with its own L2.  Mapping block b to tile
 // (b % 8) * (G / 8) + b / 8 gives every XCD a contiguous band of tiles, so the
 // stencil's halo rows are mostly read from the XCD's own L2.  Identity when G
-// is not a multiple of 8.  back: the same bands, each from its end.
-__device__ __forceinline__ int xcd_tile(int b, int G, bool back = false) {
+// is not a multiple of 8.
+__device__ __forceinline__ int xcd_tile(int b, int G) {
+  if (G & 7) return b;
+  return (b & 7) * (G >> 3) + (b >> 3);
+}
+// back: the same bands, each from its end.
+__device__ __forceinline__ int xcd_tile(int b, int G, bool back) {
   if (G & 7) return back ? G - 1 - b : b;
   const int per = G >> 3, q = b >> 3;
   return (b & 7) * per + (back ? per - 1 - q : q);

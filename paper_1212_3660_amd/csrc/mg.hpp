@@ -234,18 +234,20 @@ constexpr size_t WALK_BACK = size_t(96) << 20;
 template <typename R> __device__ __forceinline__ bool walk_back(const LevelDims& f, int lS) {
   return ((size_t)f.n() << lS) * sizeof(cx<R>) >= WALK_BACK;
 }
+// EITHER: the direction is back's; else forwards.
+template <bool EITHER = false>
 __device__ __forceinline__ void xcd_block3(int& bx, int& by, int& bz, bool back = false) {
   const int gx = gridDim.x, gy = gridDim.y;
   const int w = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
   if (gridDim.z > 1 && (gy & 7) == 0) {
-    const int ry = gy >> 3, n8 = gx * ry * gridDim.z, u = back ? n8 - 1 - (w >> 3) : w >> 3;
+    const int ry = gy >> 3, n8 = gx * ry * gridDim.z, u = EITHER && back ? n8 - 1 - (w >> 3) : w >> 3;
     bx = u % gx;
     const int r = u / gx;
     by = (w & 7) * ry + r % ry;
     bz = r / ry;
     return;
   }
-  const int T = xcd_tile(w, gx * gy * gridDim.z, back);
+  const int G = gx * gy * gridDim.z, T = EITHER ? xcd_tile(w, G, back) : xcd_tile(w, G);
   const int r = T / gx;
   bx = T - r * gx;
   by = r % gy;
@@ -415,7 +417,7 @@ __global__ void __launch_bounds__(BS) k_mg_up_lanes(Op op, LevelDims f, LevelDim
   constexpr int NB = Op::NB;
   int flag = *all_done;
   int bx, j, k;
-  xcd_block3(bx, j, k, walk_back<R>(f, lS));
+  xcd_block3<true>(bx, j, k, walk_back<R>(f, lS));
   const int t = bx * BS + threadIdx.x;
   if (t >= (f.nx << lNC)) return;
   const int lc = t & ((1 << lNC) - 1), i = t >> lNC;
@@ -498,7 +500,7 @@ __global__ void __launch_bounds__(BS) k_mg_leg_rows(Op op, LevelDims f, LevelDim
   const int flag = *all_done;
   const int NC = 1 << lNC, S = 1 << lS, SW = BS >> lNC;
   const int nseg = (f.nx + SW - 1) / SW;
-  const int tile = xcd_tile(blockIdx.x, gridDim.x, UP && walk_back<R>(f, lS));
+  const int tile = UP ? xcd_tile(blockIdx.x, gridDim.x, walk_back<R>(f, lS)) : xcd_tile(blockIdx.x, gridDim.x);
   const int seg = tile % nseg, rb = tile / nseg;
   const int lc = (int)threadIdx.x & (NC - 1), ci = (int)threadIdx.x >> lNC;
   const int i = seg * SW + ci;
@@ -962,7 +964,7 @@ __global__ void __launch_bounds__(T3T) k_mg_leg_tile3(Op op, LevelDims f, LevelD
   __shared__ cx<R> stg[UP ? 1 : T3Y][UP ? 1 : T3X][LT];   // restriction: the children's sums
   const int flag = *all_done;
   int bxc, by, bz;
-  xcd_block3(bxc, by, bz, UP && walk_back<R>(f, lS));
+  xcd_block3<UP>(bxc, by, bz, UP && walk_back<R>(f, lS));
   const int ch = bxc % C, bx = bxc / C;
   if (!chunk_live<LT>(sc, ch * LT)) return;   // the block's chunk has stopped (uniform)
   const int tx = (int)threadIdx.x % T3X, ty = (int)threadIdx.x / T3X;
