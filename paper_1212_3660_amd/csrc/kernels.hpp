@@ -1707,7 +1707,8 @@ __global__ void __launch_bounds__(BS) k_assemble_lds(long n, int S, int s_real, 
 // ------------------------------------------------------ true residuals -----
 // Partial ||b_r - (K + sigma_j M) x_{j,r}||^2 (mode 0) or conj(rs_r)^T
 // (b_r - (K + sigma_j M) x_{j,r}) (mode 1) per block; blockIdx.y = shift,
-// blockIdx.z = rhs; cells over blockIdx.x.  CSR problems and small grids; larger ones use k_resid_fv.
+// blockIdx.z = rhs; cells over blockIdx.x.  General sparse K, and grids that
+// k_resid_fv's tiles do not fit (residual_rows).
 template <typename Op>
 __global__ void __launch_bounds__(BS) k_resid(Op op, long n, int S, int nf, const c128* __restrict__ sigma,
                                               const c128* __restrict__ bint, const c128* __restrict__ X,
