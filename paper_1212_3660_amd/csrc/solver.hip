@@ -2274,15 +2274,19 @@ template <typename R, typename Op, typename OpD> struct Group {
   }
 };
 
-// Launch of k_resid_fv for JR shifts a block; returns the partials' grid: at most
-// Gr blocks, each with the same number of tiles (in XCD bands a remainder would
-// all go to the first XCDs: a call on 96^3, 288 tiles, 50 shifts, takes 510 us with
-// 256 blocks, 348 with 144), none without one.
+// Blocks along x of k_resid_fv, at most Gr: each has the same number of tiles (in XCD
+// bands a remainder would all go to the first XCDs: a call on 96^3, 288 tiles, 50
+// shifts, takes 510 us with 256 blocks, 348 with 144), none is without one.
+template <typename OpD> static int resid_march_grid(const OpD& opd, int Gr) {
+  const int tiles = resid_fv_tiles(opd), each = (tiles + Gr - 1) / Gr;
+  return each == 1 ? tiles : std::min(((tiles + each - 1) / each + 7) & ~7, Gr);
+}
+
+// Launch of k_resid_fv for JR shifts a block; returns the partials' grid.
 template <int JR, typename OpD>
 static int resid_march(const OpD& opd, int Gr, int S, int s_real, int nf, const c128* sigma, const c128* bint,
                        const c128* X, const c128* rs, int mode, c128* rpart, hipStream_t st) {
-  const int tiles = resid_fv_tiles(opd), each = (tiles + Gr - 1) / Gr;
-  Gr = each == 1 ? tiles : std::min(((tiles + each - 1) / each + 7) & ~7, Gr);
+  Gr = resid_march_grid(opd, Gr);
   const dim3 g(Gr, (nf + JR - 1) / JR, s_real);
   if (mode == 0) k_resid_fv<OpD, JR, 0><<<g, BS, 0, st>>>(opd, S, nf, sigma, bint, X, rs, rpart);
   else k_resid_fv<OpD, JR, 1><<<g, BS, 0, st>>>(opd, S, nf, sigma, bint, X, rs, rpart);
@@ -2300,22 +2304,32 @@ static int residual_rows(const OpD& opd, long n, int S, int s_real, int nf, cons
   // is padding (one lane, kernels alone, marched and not: 1048576 x 1 cells, 8
   // shifts: 3.3 ms, 0.04; 10485 x 100, 8 shifts: 62 us, 47; 13981 x 300, 3 shifts:
   // 146, 129; 64 x 128 x 16, 100 shifts, a quarter in use: 152, 102).  And it is a
-  // chain of round trips over few waves, which wants 4 Mi entries of X (512^2, 20
-  // shifts, 5 Mi: 28, 35; 3495 x 300, 3 Mi: 39, 31), in 3-D, where a tile is read
-  // with the planes beside it, 16 Mi unless several lanes share its b (64^3, 50
-  // shifts, 12.5 Mi: 113, 98; 100 shifts: 184, 241).  In 2-D below 8 Mi or 16
-  // shifts the gain at full use is 1.2 to 1.5, so 0.6 of the lanes and shifts have
-  // to be in use; elsewhere it is 1.5 to 2, and 0.38 are enough (10485 x 100, 20
-  // shifts, 0.39: 136, 162).
+  // chain of round trips over few waves, which wants 4 Mi entries of X, in 2-D with
+  // full tiles 3 Mi (256 x 256, 50 shifts, 3.1 Mi: 24, 28; 3495 x 300, 3 shifts, 3 Mi,
+  // 0.44 in use: 39, 31; four lanes 64 x 256, 50 shifts, 3.1 Mi: 0.95 of the rate).
+  // 0.37 of the lanes and shifts in use are enough (10485 x 100, 20 shifts, 0.39: 136,
+  // 162; 50, 0.376: 254, 390) from 16 Mi entries, for several lanes, which share b,
+  // and in 2-D from 16 shifts and 4 Mi.  Elsewhere the gain at full use is 1.2 to 1.5,
+  // and 0.6 have to be in use (5 shifts: 3276 x 320, 5 Mi, 0.39: 46, 36).  There a 3-D
+  // march, whose tiles are read with the planes beside them, also has to put a block
+  // on each of the 256 CUs in every round of three a CU (150 registers), the last one
+  // too: 128 x 64 x 192, 3 shifts, 192 blocks 57, 52; 128 x 16 x 256, 16 shifts, 512
+  // blocks 40, 69; 64 x 64 x 192, 16 shifts, 768 blocks 72, 95; 64^3, 50 shifts, 832
+  // blocks 110, 98; 128 x 64 x 96, 16 shifts, 1024 blocks 74, 94.
   bool march = false;
   if constexpr (OpD::NB > 0) {
     constexpr bool D3 = OpD::NB == 6;
-    const bool lanes = S >= 4;
+    constexpr long Mi = 1L << 20;
+    const int JR = S >= 4 ? 8 : 4, groups = (nf + JR - 1) / JR;
     const long items = n * nf * s_real;
-    const int JR = lanes ? 8 : 4;
-    const double used = resid_fv_share(opd) * nf / (JR * (double)((nf + JR - 1) / JR));
-    march = items >= (D3 && !lanes ? 16L << 20 : 4L << 20) &&
-            used >= (!D3 && !lanes && (nf < 16 || items < (8L << 20)) ? 0.6 : 0.38);
+    const double used = resid_fv_share(opd) * nf / (JR * (double)groups);
+    const bool wide = S >= 4 || items >= 16 * Mi;
+    march = items >= (D3 || wide ? 4 : 3) * Mi &&
+            used >= (wide || (!D3 && nf >= 16 && items >= 4 * Mi) ? 0.37 : 0.6);
+    if (D3 && !wide) {
+      const long last = (long)resid_march_grid(opd, Gr) * groups * s_real % (3 * 256);
+      march = march && (last == 0 || last >= 256);
+    }
   }
   if (march) {
     // With several lanes a line of b holds the cell's other lanes and comes once

@@ -1,6 +1,7 @@
 """True residuals of one lane on both sides of the rule that picks the kernel:
-entries of X (4 Mi in 2-D, 16 Mi in 3-D), the part of the marching kernel's
-lanes and shifts in use, thin grids and few shifts, against the oracle's operator.
+entries of X (3, 4 and 16 Mi), the part of the marching kernel's lanes and shifts
+in use, thin grids and few shifts, the last round of blocks in 3-D, against the oracle's
+operator.
 
 Tolerance: FP64 sums of at most 400,000 terms without cancellation, off by at most
 about 650 roundings of 1.1e-16: 1e-12 relative."""
@@ -13,11 +14,14 @@ from tests.gpu_util import require_gpu, announce
 
 pytestmark = pytest.mark.gpu
 
-CASES = [((129, 250), 128), ((129, 250), 131), ((129, 250), 133),     # 4 Mi is 130.1 shifts
-         ((655, 97), 64), ((655, 97), 133), ((655, 97), 141),         # 0.38 of the lanes in use, from 8 Mi
+CASES = [((129, 250), 97), ((129, 250), 98), ((129, 250), 128), ((129, 250), 131), ((129, 250), 133),     # 3 Mi is 97.5 shifts, 4 Mi 130.1
+         ((655, 97), 64), ((655, 97), 68), ((655, 97), 133), ((655, 97), 141),   # 0.38 of the lanes in use, 4 Mi is 66.02
          ((1400, 600), 5), ((1400, 600), 8),                          # 0.49 and 0.78 in use, over 4 Mi
          ((65536, 1), 70), ((30000, 3), 50), ((400000, 2), 6),        # thin
-         ((5, 17, 70), 2825), ((4, 16, 64), 4095), ((4, 16, 64), 4097), ((17, 33, 63), 476), ((3, 50, 130), 900)]
+         ((5, 17, 70), 2825), ((4, 16, 64), 4095), ((4, 16, 64), 4097), ((17, 33, 63), 476), ((3, 50, 130), 900),
+         # 12 blocks for every four shifts: under 4 Mi, over it, 768 blocks, 780, 1020, 1032
+         ((7, 33, 125), 145), ((7, 33, 125), 146), ((7, 33, 125), 256), ((7, 33, 125), 257), ((7, 33, 125), 340), ((7, 33, 125), 344),
+         ((4, 16, 64), 1023), ((4, 16, 64), 1024), ((4, 16, 64), 3072), ((4, 16, 64), 3073)]
 
 
 @pytest.mark.parametrize("shape,nf", CASES)
